@@ -104,10 +104,10 @@ Workspace layout(const jacap_config* c, const jacap_batch* b, bool greedy = fals
            U * (int64_t)((maxn + w.lchunk - 1) / w.lchunk) < kLevMinBlocks)
       w.lchunk /= 2;
   w.lchunks = (maxn + w.lchunk - 1) / w.lchunk;
-  // The fp64 Gram pass (every unit of fp32 keys; the units of bf16 keys that
-  // need it): about kPrecisePartials partials per batch, so that its buffer
-  // stays bounded at any unit count, and no chunk below kGChunkPrecise tokens
-  // (whole 32-token steps).
+  // The fp64 Gram pass: about kPrecisePartials partials per batch, so that its
+  // buffer stays bounded at any unit count, and no chunk below kGChunkPrecise
+  // tokens (whole 32-token steps). Every unit of fp32 keys is cut this way; the
+  // marked units of bf16 keys share the buffer's partials (refine_cut).
   {
     const int64_t want = std::max<int64_t>(1, kPrecisePartials / std::max<int64_t>(U, 1));
     const int64_t most = std::max<int64_t>(1, (maxn + kGChunkPrecise - 1) / kGChunkPrecise);
@@ -115,15 +115,13 @@ Workspace layout(const jacap_config* c, const jacap_batch* b, bool greedy = fals
     const int64_t per = std::max<int64_t>(kGChunkPrecise, ((maxn + np - 1) / np + 31) / 32 * 32);
     w.pchunk = (int)per;
     w.pchunks = maxn > 0 ? (int)((maxn + per - 1) / per) : 0;
+    w.pslots = (int)std::min<int64_t>(U * w.pchunks, INT32_MAX);
   }
-  // fp64 leverage chunks: kLChunkRefine tokens for the marked bf16 units;
-  // for fp32 inputs kLChunkPrecise, halved (down to kLChunkPreciseMin) while
-  // the grid would have fewer than kLevMinBlocks blocks.
-  w.plchunk = w.mfma ? kLChunkRefine : kLChunkPrecise;
-  if (!w.mfma)
-    while (w.plchunk > kLChunkPreciseMin &&
-           U * (int64_t)((maxn + w.plchunk - 1) / w.plchunk) < kLevMinBlocks)
-      w.plchunk /= 2;
+  // fp64 leverage chunks of fp32 inputs: kLChunkPrecise tokens, halved (down to
+  // kLChunkPreciseMin) while the halved chunks still run in one round, two per
+  // compute unit (a second, nearly empty round costs as much as the first).
+  w.plchunk = kLChunkPrecise;
+  while (w.plchunk > kLChunkPreciseMin && 2 * LHT / w.plchunk <= kRefineBlocks) w.plchunk /= 2;
   w.plchunks = (maxn + w.plchunk - 1) / w.plchunk;
   const int64_t NB = D / 16;
   const int64_t npair = NB * (NB + 1) / 2;
@@ -132,13 +130,13 @@ Workspace layout(const jacap_config* c, const jacap_batch* b, bool greedy = fals
   const int64_t fp64_part_bytes = U * (int64_t)w.pchunks * npair * 256 * 8;
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t r = o; o = align256(o + bytes); return r; };
-  w.status = take(4);
+  w.status = take(8);
   w.uflags = take(4 * U);
   w.mu = take(8 * U * D);
   w.lam = take(8 * U * D);
   w.lamfull = take(c->cov_mode == JACAP_COV_FULL ? 4 * U * D * D : 4);
-  w.smax_m = take(4 * U);
-  w.smax_z = take(8 * U);
+  w.rlist = take(4 * U);
+  take(8 * U);  // held in reserve: the size of a workspace is part of the interface
   w.wscale = take(8 * U);
   w.z = take(4 * LHT);
   w.kappa = take(4 * LHT);

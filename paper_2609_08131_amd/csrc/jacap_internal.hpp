@@ -23,14 +23,15 @@ constexpr int kGChunkMfma = 512;     // tokens per workgroup in the MFMA Gram pa
 constexpr int kGChunkMfmaMax = 16384; // ... and at most (larger chunks: fewer partial Grams)
 constexpr int kGramMinBlocks = 2048;  // chunks are as large as this many blocks in the grid allow
 constexpr int kGramSpan = 128;       // tokens between two flushes of the Gram's short fp32 chains
-constexpr int kGChunkPrecise = 128;  // tokens per workgroup in the fp64 Gram pass: at least
+constexpr int kGChunkPrecise = 128;  // tokens per chunk of the fp64 Gram pass: at least
 constexpr int kPrecisePartials = 256;  // fp64 Gram partials per batch the chunking aims at
+constexpr int kRefineChunks = 16;      // fp64 Gram partials of one marked bf16 unit: at most
 constexpr int kLChunkMfma = 4096;    // tokens per workgroup in the MFMA leverage pass: at most
 constexpr int kLChunkMfmaMin = 256;  // ... and at least (batches too small to fill the chip)
 constexpr int kLevMinBlocks = 2048;  // leverage chunks shrink until the grid has this many blocks
 constexpr int kLChunkPrecise = 1024; // tokens per workgroup in the fp64 leverage pass (fp32 keys):
-constexpr int kLChunkPreciseMin = 64; // ... at most, and at least (small batches)
-constexpr int kLChunkRefine = 4096;  // ... and over the bf16 units that take the fp64 path
+constexpr int kLChunkPreciseMin = 128; // ... at most, and at least (small batches; one workgroup trip)
+constexpr int kLRefineItems = 2048;  // the marked bf16 units are cut into about this many chunks
 constexpr int kWChunk = 4096;        // tokens per workgroup in the weight pass
 // The K pass sums a chunk's exp(z - max) terms (all but the max's own) as
 // exp(z - max + kRestShift) in fp32, so that they stay normal down to
@@ -139,12 +140,27 @@ __device__ __forceinline__ bool grid_unit_chunk(const Geo& g, int nchunks, int& 
   return grid_unit_chunk_at<CHUNK_MAJOR>(g, nchunks, blockIdx.x, u, chunk);
 }
 
-// Workgroups of the kernels that serve only the units marked for the fp64 path
-// (usually none or few): they walk the (unit, chunk) items in a grid-stride
-// loop and skip unmarked units, so a launch costs a few microseconds however
-// many units and chunks the batch has.
-constexpr int kRefineBlocks = 512;
 constexpr int kComputeUnits = 256;  // MI355X
+// Workgroups of the fp64 kernels that serve only the units marked for the fp64
+// path (usually none or few): they walk the items of the marked units' list
+// in a grid-stride loop, so a launch with an empty list costs a few
+// microseconds however many units and chunks the batch has. Two per compute
+// unit, which is what their LDS allows.
+constexpr int kRefineBlocks = 2 * kComputeUnits;
+
+// How the fp64 Gram cuts the R marked units: every unit into `nch` chunks of
+// `tok` tokens (whole kGChunkPrecise), the more of them the fewer units share
+// the buffer's `slots` partials, at most kRefineChunks (the factorisation sums
+// a unit's partials in one workgroup). Partial of list entry li, chunk c:
+// slot li * nch + c.
+struct RefineCut { int nch, tok; };
+__device__ __forceinline__ RefineCut refine_cut(int R, int maxn, int slots) {
+  int nch = min(min(max(slots / max(R, 1), 1), kRefineChunks),
+                (maxn + kGChunkPrecise - 1) / kGChunkPrecise);
+  nch = max(nch, 1);
+  const int tok = ((maxn + nch - 1) / nch + kGChunkPrecise - 1) / kGChunkPrecise * kGChunkPrecise;
+  return {(maxn + tok - 1) / tok, tok};
+}
 
 inline int64_t chunked_grid(const Geo& g, int nchunks) {
   const int64_t pairs = (int64_t)nchunks * (g.U / g.V);
@@ -155,13 +171,12 @@ inline int64_t chunked_grid(const Geo& g, int nchunks) {
 // Workspace layout (byte offsets from the workspace base; 256-byte aligned)
 // ---------------------------------------------------------------------------
 struct Workspace {
-  size_t status;   // uint32: OR of the public flags
+  size_t status;   // uint32: OR of the public flags; then uint32: the marked units' count
   size_t uflags;   // uint32 [U]
   size_t mu;       // double [U][D]
   size_t lam;      // double [U][D]          (diagonal covariance)
   size_t lamfull;  // float  [U][D][D]       (full covariance, FULL mode only)
-  size_t smax_m;   // float  [U]             global logit max
-  size_t smax_z;   // double [U]             global sum of exp(z - m)
+  size_t rlist;    // int32  [U]             the units marked for the fp64 path, in no given order
   size_t wscale;   // double [U]             power of two by which the stored weights are scaled
   size_t z;        // float  [L][H][T]       centre logits
   size_t kappa;    // float  [L][H][T]       query response
@@ -170,18 +185,19 @@ struct Workspace {
   size_t hscore;   // float  [L][H][G][T]    per-query-head scores (per-head GQA mode)
   size_t kept;     // int32  [B][L][H][budget] kept positions, staged by jacap_select_evicted
   size_t gram;     // per-chunk partial Grams: [U][gchunks][NPAIR*256] fp32 (bf16 MFMA pass)
-                   // or [U][pchunks][NPAIR*256] fp64 (fp64 pass); one buffer for both
-  size_t gram_red; // double [U][NPAIR*256]  the reduced Gram (gram_reduced), block-lane
-                   // layout; after an fp64 factorisation, L^{-1} in the lower-block
-                   // layout (see k_factor.hip)
+                   // or fp64 partials, pslots of NPAIR*256 (fp64 pass); one buffer for both
+  size_t gram_red; // double [U][NPAIR*256]  the reduced Gram (gram_reduced), in its partials'
+                   // layout; after an fp64 factorisation, L^{-1} in fp64 MFMA operand
+                   // order (see k_factor.hip)
   size_t lfrag;    // bf16 [U][NLP][2][64][8] L^{-1} hi/lo MFMA B fragments, bf16 path
   size_t gc;       // double [L][H][T]       greedy: c_i when last computed
   size_t gst;      // int32  [L][H][T]       greedy: picks made at that time (-1 = taken)
   size_t gent;     // GreedyEntry [U][ceil(maxn / 256)]  greedy: best of each 256-position block
   size_t total;
   int kchunks, wchunks, gchunks, gchunk, gparts, lchunks, lchunk;
-  int pchunks, pchunk;  // chunks of the fp64 Gram pass
-  int plchunks, plchunk;  // chunks of the fp64 leverage pass
+  int pchunks, pchunk;  // chunks of the fp64 Gram pass over every unit (fp32 inputs)
+  int pslots;           // fp64 partials the Gram buffer holds
+  int plchunks, plchunk;  // chunks of the fp64 leverage pass over every unit
   bool mfma;       // bf16 path (MFMA Gram and leverage)
 };
 
@@ -320,6 +336,38 @@ __device__ __forceinline__ float buffer_load_f32(__amdgpu_buffer_rsrc_t r, int32
 __device__ __forceinline__ void drain_vmem() {
   // s_waitcnt encoding (gfx9): vmcnt = 0, expcnt = 7, lgkmcnt = 15 (no wait).
   __builtin_amdgcn_s_waitcnt(0x0F70);
+}
+
+// D += A B on the fp64 MFMA (16x16x4): lane l supplies A[l % 16][l / 16] and
+// B[l / 16][l % 16]; element i of lane l's result is D[4 i + l / 16][l % 16].
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 acc) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+}
+
+// WORDS consecutive 32-bit words at byte offset `off` of a buffer range.
+template <int WORDS>
+__device__ __forceinline__ void buffer_load_words(__amdgpu_buffer_rsrc_t r, int32_t off,
+                                                  uint32_t (&x)[WORDS]) {
+  static_assert(WORDS == 2 || WORDS % 4 == 0, "8- or 16-byte loads");
+  if constexpr (WORDS == 2) {
+    const auto y = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+    x[0] = y[0]; x[1] = y[1];
+  } else {
+#pragma unroll
+    for (int i = 0; i < WORDS / 4; ++i) {
+      const uint4 y = buffer_load16(r, off + 16 * i);
+      x[4 * i] = y.x; x[4 * i + 1] = y.y; x[4 * i + 2] = y.z; x[4 * i + 3] = y.w;
+    }
+  }
+}
+// Element e of a run of bf16 (uint16_t) or fp32 elements held in 32-bit words.
+template <typename T, int WORDS>
+__device__ __forceinline__ double word_elem(const uint32_t (&x)[WORDS], int e) {
+  if constexpr (sizeof(T) == 2)
+    return (double)__uint_as_float((e & 1) ? x[e >> 1] & 0xFFFF0000u : x[e >> 1] << 16);
+  else
+    return (double)__uint_as_float(x[e]);
 }
 
 // ---------------------------------------------------------------------------

@@ -3,18 +3,16 @@
 // the triangular inverse L^{-1}, one workgroup per unit, in fp64 in LDS.
 // ||L^{-1} v||^2 = v^T A^{-1} v is what the leverage score of Eq. 10 needs.
 //
-// Input: the unit's Gram in block-lane layout (upper 16x16 blocks, see
-// k_gram.hip): its per-chunk partials, summed here in chunk order in fp64, or
-// (units of many chunks) the reduce kernel's sum of them. Output, after the
+// Input: the unit's Gram in the layout of its pass (see k_gram.hip): its
+// per-chunk partials, summed here in chunk order in fp64, or (units of many
+// chunks) the reduce kernel's sum of them. Output, after the
 // first factorisation of an fp32-accumulated
 // Gram (bf16 inputs): L^{-1} rounded to fp32 and split into bf16 hi + lo
 // terms, stored directly in the per-lane B-fragment order of the 16x16x32
 // MFMA (only the K-blocks that touch the lower triangle). After a
 // factorisation of an fp64 Gram (fp32 inputs; the bf16 units marked for the
 // fp64 path): L^{-1} in fp64, over the unit's slot of the reduced-Gram buffer
-// in the lower-block layout -- block pair p = pair_index(i, j), i <= j, holds the
-// 16x16 block X[16 j + r][16 i + c] at p * 256 + 16 r + c (zero above the
-// diagonal of a diagonal block).
+// in the operand order of the fp64 leverage pass (store_lower_f64).
 //
 // Blocked algorithm on 16x16 blocks (the sequential chain is what bounds a
 // single workgroup, so the work between barriers is made as wide as possible):
@@ -101,8 +99,6 @@ __device__ __forceinline__ double rsqrt_f64(double x) {
   return y;
 }
 
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-
 // LDS layout of A (and of L, then X = L^{-1}, which replace it): only the
 // lower 16x16 blocks (I >= J), packed by rows of blocks; block (I, J) starts
 // at (I (I + 1) / 2 + J) * kBlk and holds element (r, c) at r * kBP + c. The
@@ -113,12 +109,6 @@ constexpr int kBlk = 16 * kBP;
 __device__ __forceinline__ int lidx(int row, int col) {
   const int I = row >> 4, J = col >> 4;
   return (I * (I + 1) / 2 + J) * kBlk + (row & 15) * kBP + (col & 15);
-}
-
-// D += A B on the fp64 MFMA (16x16x4): lane l supplies A[l % 16][l / 16] and
-// B[l / 16][l % 16]; element i of lane l's result is D[4 i + l / 16][l % 16].
-__device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 acc) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
 }
 
 // Lower-triangle index e -> (row i, column j), j <= i (row-major over the triangle).
@@ -170,6 +160,22 @@ __device__ __forceinline__ void store_lower_frags(uint16_t* __restrict__ out, F 
     uint16_t* dl = out + ((int64_t)(qp * 2 + 1) * 64 + ln) * 8;
 #pragma unroll
     for (int t = 0; t < 8; ++t) { dh[t] = hi[t]; dl[t] = lo[t]; }
+  }
+}
+
+// A lower-triangular matrix (x(a, b) for b <= a) in fp64, in the order in which
+// the fp64 leverage pass supplies it to the MFMA 16x16x4: block (J, B), B <= J, at
+// (J (J + 1) / 2 + B) * 256; its K-step s of lane l at (s / 2) * 128 + 2 l + s % 2,
+// holding X[16 J + l % 16][16 B + 4 (l / 16) + s] (zero above the diagonal).
+template <int D, typename F>
+__device__ __forceinline__ void store_lower_f64(double* __restrict__ out, F x) {
+  constexpr int NB = D / 16;
+  for (int e = threadIdx.x; e < NB * (NB + 1) / 2 * 256; e += blockDim.x) {
+    int J, B;
+    tri_index(e >> 8, J, B);
+    const int l = (e >> 1) & 63, s = 2 * ((e >> 7) & 1) + (e & 1);
+    const int a = 16 * J + (l & 15), b = 16 * B + 4 * (l >> 4) + s;
+    out[e] = b <= a ? x(a, b) : 0.0;
   }
 }
 
@@ -311,21 +317,31 @@ __device__ __forceinline__ int cholesky_lds(double* A, const double* dg, double*
   return 0;
 }
 
+// The units that the first factorisation of bf16 inputs marks for the fp64
+// path: their count and list (any order), beside the per-unit flag.
+struct Marked {
+  uint32_t* count;
+  int32_t* list;
+  __device__ __forceinline__ void add(int u, uint32_t* uflags) const {
+    atomicOr(uflags + u, kUnitRefine);
+    list[atomicAdd(count, 1u)] = u;
+  }
+};
+
 // One unit. Its Gram: PASS 0 (all units) reads the reduced Gram `red` if the
 // reduce kernel ran (`reduced`), else sums here, in chunk order, in fp64, the
 // fp32 MFMA partials `part32` (bf16 inputs; gchunks per unit of gchunk tokens)
-// or the fp64 partials `part` (fp32 inputs; pchunks of pchunk tokens) -- the
-// reduce kernel's arithmetic; PASS 1 (the units of bf16 inputs that pass 0
-// marked kUnitRefine) sums its fp64 partials. FRAGS: bf16 inputs.
-template <int D, bool FRAGS, int NT>
+// or the unit's nch64 fp64 partials `part` (fp32 inputs) -- the reduce kernel's
+// arithmetic; PASS 1 (the units of bf16 inputs that pass 0 marked) sums its
+// fp64 partials. FRAGS: bf16 inputs.
+template <int D, bool FRAGS, int NT, int PASS>
 __device__ __forceinline__ void factor_unit(const Geo& g, int u, double* __restrict__ red,
-                                            const double* __restrict__ part, int pchunks,
-                                            int pchunk, const float* __restrict__ part32,
-                                            int gchunks, int gchunk, bool reduced,
-                                            double ridge,
-                                            const double* __restrict__ wscale, int pass,
+                                            const double* __restrict__ part, int nch64,
+                                            const float* __restrict__ part32, int gchunks,
+                                            int gchunk, bool reduced, double ridge,
+                                            const double* __restrict__ wscale,
                                             uint16_t* __restrict__ lfrag, uint32_t* status,
-                                            uint32_t* uflags) {
+                                            uint32_t* uflags, const Marked& marked) {
   constexpr int NB = D / 16;
   constexpr int NPAIR = NB * (NB + 1) / 2;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -333,8 +349,8 @@ __device__ __forceinline__ void factor_unit(const Geo& g, int u, double* __restr
   if (un.n == 0) return;
   // The fp32-accumulated Gram of bf16 inputs may be redone in fp64 later;
   // singularity is decided on an fp64 Gram only (pass 1, or fp32 inputs).
-  const bool may_refine = FRAGS && pass == 0;
-  const double piv_rel =
+  constexpr bool may_refine = FRAGS && PASS == 0;
+  constexpr double piv_rel =
       may_refine ? kPivRelRefine : (FRAGS ? kPivRelSingularBf16 : kPivRelSingularFp32);
 
   __shared__ double A[NB * (NB + 1) / 2 * kBlk];  // lower 16x16 blocks, see lidx
@@ -355,7 +371,7 @@ __device__ __forceinline__ void factor_unit(const Geo& g, int u, double* __restr
   constexpr int CHU = PER <= 9 ? 2 : 1;
 #pragma unroll
   for (int k = 0; k < PER; ++k) rv[k] = make_double2(0.0, 0.0);
-  if (reduced && pass == 0) {
+  if (PASS == 0 && reduced) {
     const double2* R = reinterpret_cast<const double2*>(red + (int64_t)u * (NPAIR * 256));
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
@@ -378,10 +394,9 @@ __device__ __forceinline__ void factor_unit(const Geo& g, int u, double* __restr
       }
     }
   } else {  // fp64 partials
-    const int nch = (un.n + pchunk - 1) / pchunk;
-    const double2* P = reinterpret_cast<const double2*>(part + (int64_t)u * pchunks * (NPAIR * 256));
+    const double2* P = reinterpret_cast<const double2*>(part);
 #pragma unroll CHU
-    for (int c = 0; c < nch; ++c) {
+    for (int c = 0; c < nch64; ++c) {
 #pragma unroll
       for (int k = 0; k < PER; ++k) {
         const int e2 = tid + k * NT;
@@ -403,11 +418,20 @@ __device__ __forceinline__ void factor_unit(const Geo& g, int u, double* __restr
       for (int q = 0; q < NB; ++q)
         if (p >= NB - bi) { p -= NB - bi; ++bi; }
       const int bj = bi + p;
-      const int ln = (e & 255) / 4, r = e % 4;  // r even: entries r and r + 1 of lane ln
-      const int row = bi * 16 + (ln >> 4) * 4 + r;
-      const int col = bj * 16 + (ln & 15);
-      if (row <= col) A[lidx(col, row)] = rv[k].x;  // diagonal block: upper half only
-      if (row + 1 <= col) A[lidx(col, row + 1)] = rv[k].y;
+      if (may_refine) {  // block-lane layout
+        const int ln = (e & 255) / 4, r = e % 4;  // r even: entries r and r + 1 of lane ln
+        const int row = bi * 16 + (ln >> 4) * 4 + r;
+        const int col = bj * 16 + (ln & 15);
+        if (row <= col) A[lidx(col, row)] = rv[k].x;  // diagonal block: upper half only
+        if (row + 1 <= col) A[lidx(col, row + 1)] = rv[k].y;
+      } else {  // the fp64 pass's layout: channels NB (4 i + l / 16) + bi, NB (l % 16) + bj
+        const int i = (e >> 6) & 3, l = e & 63;  // l even: entries of lanes l and l + 1
+        const int ra = NB * (4 * i + (l >> 4)) + bi, cb = NB * (l & 15) + bj;
+        // bi == bj: an entry and its mirror image, the upper one left out
+        if (bi != bj || ra >= cb) A[lidx(max(ra, cb), min(ra, cb))] = rv[k].x;
+        const int cb1 = cb + NB;
+        if (bi != bj || ra >= cb1) A[lidx(max(ra, cb1), min(ra, cb1))] = rv[k].y;
+      }
     }
   }
   if (tid == 0) bad = 0;
@@ -489,7 +513,7 @@ __device__ __forceinline__ void factor_unit(const Geo& g, int u, double* __restr
                  : cholesky_lds<D, NT, true>(A, dg, idg, &bad, piv_rel, (int)kUnitSingular);
   if (code) {
     if (tid == 0) {
-      if (code == (int)kUnitRefine) atomicOr(uflags + u, kUnitRefine);
+      if (code == (int)kUnitRefine) marked.add(u, uflags);
       else raise_flags(status, uflags, u, (uint32_t)code);
     }
     return;
@@ -613,49 +637,50 @@ __device__ __forceinline__ void factor_unit(const Geo& g, int u, double* __restr
       x1 = fmax(x1, red_sh2[w]);
     }
     if (anorm * x1 * xinf > kRefineCond) {
-      if (tid == 0) atomicOr(uflags + u, kUnitRefine);
+      if (tid == 0) marked.add(u, uflags);
       return;  // pass 1 writes this unit's L^{-1}
     }
   }
 
   // Store L^{-1}.
   if (!may_refine) {  // fp64, over the unit's slot of the reduced-Gram buffer
-    double* o64 = red + (int64_t)u * (NPAIR * 256);
-    for (int e = tid; e < NPAIR * 256; e += NT) {
-      int p = e >> 8, bi = 0;  // block pair p -> (bi, bj), bi <= bj
-#pragma unroll
-      for (int q = 0; q < NB; ++q)
-        if (p >= NB - bi) { p -= NB - bi; ++bi; }
-      const int bj = bi + p;
-      o64[e] = xinv(16 * bj + ((e >> 4) & 15), 16 * bi + (e & 15));
-    }
+    store_lower_f64<D>(red + (int64_t)u * (NPAIR * 256), xinv);
   } else {
     store_lower_frags<D>(lfrag + (int64_t)u * lower_frag_elems(D), xinv);
   }
 }
 
-// PASS 0: one workgroup per unit. PASS 1: a grid-stride walk over the units
-// that skips those not marked kUnitRefine. NT threads: 512 (eight waves)
+// PASS 0: one workgroup per unit. PASS 1: a grid-stride walk over the marked
+// units' list. NT threads: 512 (eight waves)
 // when the units fit the compute units in one round; 256 (bounded to 256
 // VGPRs, so that two workgroups share a compute unit and one's sequential
 // steps overlap the other's) when there are more.
-template <int D, bool FRAGS, int NT>
+template <int D, bool FRAGS, int NT, int PASS>
 __global__ __launch_bounds__(NT, 512 / NT) void factor_kernel(
     Geo g, double* __restrict__ red, const double* __restrict__ part, int pchunks, int pchunk,
-    const float* __restrict__ part32, int gchunks, int gchunk, int reduced, double ridge,
-    const double* __restrict__ wscale, int pass, uint16_t* __restrict__ lfrag, uint32_t* status,
-    uint32_t* uflags) {
-  for (int u = blockIdx.x; u < g.U; u += gridDim.x) {
-    if (pass == 1 && !(uflags[u] & kUnitRefine)) continue;
-    factor_unit<D, FRAGS, NT>(g, u, red, part, pchunks, pchunk, part32, gchunks, gchunk,
-                              reduced != 0, ridge, wscale, pass, lfrag, status, uflags);
-    __syncthreads();  // LDS of this unit fully consumed before the next one's loads
+    int pslots, const float* __restrict__ part32, int gchunks, int gchunk, int reduced,
+    double ridge, const double* __restrict__ wscale, uint16_t* __restrict__ lfrag,
+    uint32_t* status, uint32_t* uflags, Marked marked) {
+  constexpr int64_t SZ = (D / 16) * (D / 16 + 1) / 2 * 256;
+  auto unit = [&](int u, const double* P, int tok) {
+    const int nch64 = (decode_unit(g, u).n + tok - 1) / tok;
+    factor_unit<D, FRAGS, NT, PASS>(g, u, red, P, nch64, part32, gchunks, gchunk, reduced != 0,
+                                    ridge, wscale, lfrag, status, uflags, marked);
+  };
+  if constexpr (PASS == 0) {
+    unit(blockIdx.x, part + (int64_t)blockIdx.x * pchunks * SZ, pchunk);
+  } else {
+    const int nu = (int)*marked.count;
+    const RefineCut rc = refine_cut(nu, g.maxn, pslots);
+    for (int li = blockIdx.x; li < nu; li += gridDim.x) {
+      unit(marked.list[li], part + (int64_t)li * rc.nch * SZ, rc.tok);
+      __syncthreads();  // LDS of this unit fully consumed before the next one's loads
+    }
   }
 }
 
 hipError_t launch_factor(const Launch& L, bool refine) {
   if (refine && !L.ws.mfma) return hipSuccess;
-  const int pass = refine ? 1 : 0;
   const Geo& g = L.geo;
   double* red = ws_ptr<double>(L.wsp, L.ws.gram_red);
   uint16_t* lf = ws_ptr<uint16_t>(L.wsp, L.ws.lfrag);
@@ -667,19 +692,23 @@ hipError_t launch_factor(const Launch& L, bool refine) {
   // first pass of bf16 inputs); both in the Gram buffer
   const double* part = ws_ptr<double>(L.wsp, L.ws.gram);
   const float* part32 = ws_ptr<float>(L.wsp, L.ws.gram);
-  const int blocks = refine ? std::min(g.U, kRefineBlocks) : g.U;
+  const Marked marked{st + 1, ws_ptr<int32_t>(L.wsp, L.ws.rlist)};
+  const int blocks = refine ? std::min(g.U, kComputeUnits) : g.U;
   const bool pairs = !refine && g.U > kComputeUnits;  // two workgroups per compute unit
   auto go = [&](auto kern, int nt) {
-    kern<<<blocks, nt, 0, L.stream>>>(g, red, part, L.ws.pchunks, L.ws.pchunk, part32,
+    kern<<<blocks, nt, 0, L.stream>>>(g, red, part, L.ws.pchunks, L.ws.pchunk, L.ws.pslots, part32,
                                       L.ws.gchunks, L.ws.gchunk, gram_reduced(L) ? 1 : 0, ridge,
-                                      wsc, pass, lf, st, uf);
+                                      wsc, lf, st, uf, marked);
   };
-  if (L.ws.mfma) {
-    if (g.D == 128) pairs ? go(factor_kernel<128, true, 256>, 256) : go(factor_kernel<128, true, 512>, 512);
-    else pairs ? go(factor_kernel<64, true, 256>, 256) : go(factor_kernel<64, true, 512>, 512);
+  if (refine) {
+    if (g.D == 128) go(factor_kernel<128, true, 512, 1>, 512);
+    else go(factor_kernel<64, true, 512, 1>, 512);
+  } else if (L.ws.mfma) {
+    if (g.D == 128) pairs ? go(factor_kernel<128, true, 256, 0>, 256) : go(factor_kernel<128, true, 512, 0>, 512);
+    else pairs ? go(factor_kernel<64, true, 256, 0>, 256) : go(factor_kernel<64, true, 512, 0>, 512);
   } else {
-    if (g.D == 128) pairs ? go(factor_kernel<128, false, 256>, 256) : go(factor_kernel<128, false, 512>, 512);
-    else pairs ? go(factor_kernel<64, false, 256>, 256) : go(factor_kernel<64, false, 512>, 512);
+    if (g.D == 128) pairs ? go(factor_kernel<128, false, 256, 0>, 256) : go(factor_kernel<128, false, 512, 0>, 512);
+    else pairs ? go(factor_kernel<64, false, 256, 0>, 256) : go(factor_kernel<64, false, 512, 0>, 512);
   }
   return hipGetLastError();
 }

@@ -14,8 +14,9 @@
 // matrix is ill-conditioned enough for the fp32 rounding to show in the
 // scores, and a second pass recomputes only those in fp64.
 //
-// fp64 pass (every unit of fp32 inputs; the marked units of bf16 inputs): fp64
-// VALU accumulation of exact products (register tiles), same partial layout.
+// fp64 pass (every unit of fp32 inputs; the marked units of bf16 inputs): the
+// fp64 MFMA on exact weighted operands w v, partials in a layout of its own
+// (gram_f64_kernel).
 #include <type_traits>
 
 #include <algorithm>
@@ -309,87 +310,171 @@ __global__ __launch_bounds__(kThreads, 2) void gram_mfma_kernel(
   }
 }
 
-// fp64 Gram: every unit of fp32 inputs, and (REFINE_ONLY) the units of bf16
-// inputs that the factorisation marked kUnitRefine. Products w_i v_ij v_ik are
-// exact in fp64 (a bf16 or fp32 value times an fp32 weight, times a bf16 or
-// fp32 value), the sums fp64. Thread (ty, tx) of a 16 x 16 grid owns a
-// (D/16) x (D/16) register tile of M; V is staged 32 tokens at a time. One
-// partial per chunk of `pchunk` tokens, in the block-lane layout.
-template <typename T, int D, bool REFINE_ONLY>
-__global__ __launch_bounds__(kThreads) void gram_precise_kernel(
+// ---------------------------------------------------------------------------
+// fp64 Gram: every unit of fp32 inputs, or (MARKED) the units of bf16 inputs
+// that the factorisation marked, from their list. fp64 MFMA 16x16x4 over
+// tokens: the operand w v is exact in fp64 (an fp32 weight times a bf16 or fp32
+// value), the sums are fp64.
+//
+// The kernel is bound by the fp64 matrix rate (36 of the 64 block products at
+// d = 128, 64 cycles each and SIMD), so the operands must cost nothing: channel
+// block I of the MFMA holds the channels NB r + I, r = 0 .. 15 (NB = d / 16
+// blocks), which makes lane (r, q)'s elements of all NB blocks the NB
+// consecutive channels NB r .. of token q -- one 16-byte load of a bf16 row
+// (32 bytes of an fp32 row), whole rows per wave, no LDS and no transposition.
+// M is symmetric, so the pairs I <= J cover it: M[NB r + I][NB c + J] for
+// every (r, c) (a pair of channels of one block twice, as (r, c) and (c, r)).
+//
+// A workgroup takes one chunk of a unit and one column pair {CP, NB-1-CP} of the
+// block pairs (NB + 1 products; the NB / 2 workgroups of a chunk sit 8 apart in
+// dispatch order, on one XCD, so that its L2 serves all but the first of
+// them); its eight waves take turns of NS four-token steps and their sums
+// are added in a fixed order through LDS. A unit thus spreads over NB / 2
+// workgroups of eight waves per chunk: few marked units still fill the chip.
+//
+// Measured (MI355X): 241 marked units of 8192 tokens, d = 128, bf16: 3.50 ms as
+// 16x16 register tiles on the fp64 VALU with both operands read from LDS,
+// 0.65 ms here (0.54 ms at the measured fp64 matrix rate of 72 TFLOP/s); 14
+// marked units of 2176 tokens among 4096: 986 us and 25 us.
+//
+// Partial: block pair p (row-major over I <= J), entry i of lane l at
+// p * 256 + 64 i + l = M[NB (4 i + l / 16) + I][NB (l % 16) + J].
+// ---------------------------------------------------------------------------
+constexpr int kF64Threads = 512;
+constexpr int kF64Waves = kF64Threads / 64;
+constexpr int64_t kF64Blocks = 1 << 20;  // grid over every unit: at most (a grid-stride walk)
+
+template <typename T, int D, int CP>
+__device__ __forceinline__ void gram_f64_item(const T* vb, int64_t vst, const float* wrow, int base,
+                                              int end, double* __restrict__ out, double* red) {
+  constexpr int NB = D / 16;
+  constexpr int JA = CP, JB = NB - 1 - CP;
+  constexpr int NP = JA + JB + 2;                  // block products: NB + 1
+  constexpr int WORDS = NB * sizeof(T) / 4;        // 32-bit words of a lane's NB elements
+  constexpr int NS = 2;                            // four-token steps per wave turn
+  constexpr int TURN = 4 * NS;                     // tokens per wave turn
+  const int lane = threadIdx.x & 63, r16 = lane & 15, q4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  f64x4 acc[NP];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) acc[p] = f64x4{0.0, 0.0, 0.0, 0.0};
+  struct Turn { uint32_t v[NS][WORDS]; float w[NS]; };
+  const int32_t vstb = (int32_t)vst * (int32_t)sizeof(T);
+  const int32_t voff = q4 * vstb + r16 * (int32_t)(NB * sizeof(T));
+  // Rows past the chunk's end (and their weights) load as zeros.
+  auto load = [&](int t0, Turn& tn) {
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const int ts = t0 + 4 * s;
+      const int32_t rows = min(end - ts, 4);
+      buffer_load_words<WORDS>(buffer_range(vb + (int64_t)ts * vst,
+                                            rows_bytes(rows, vstb, D * (int32_t)sizeof(T))),
+                               voff, tn.v[s]);
+      tn.w[s] = buffer_load_f32(buffer_range(wrow + ts, max(rows, 0) * 4), q4 * 4);
+    }
+    __builtin_amdgcn_sched_barrier(0);  // issued here, two turns ahead of their use
+  };
+  auto compute = [&](const Turn& tn) {
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      double x[JB + 1];
+#pragma unroll
+      for (int i = 0; i <= JB; ++i) x[i] = word_elem<T, WORDS>(tn.v[s], i);
+      const double w = (double)tn.w[s];
+      const double xa = w * x[JA], xb = w * x[JB];
+#pragma unroll
+      for (int i = 0; i <= JB; ++i) acc[JA + 1 + i] = mfma64(x[i], xb, acc[JA + 1 + i]);
+#pragma unroll
+      for (int i = 0; i <= JA; ++i) acc[i] = mfma64(x[i], xa, acc[i]);
+      __builtin_amdgcn_sched_barrier(0);  // one step's operands at a time in registers
+    }
+  };
+  constexpr int STRIDE = TURN * kF64Waves;
+  const int t_first = base + wave * TURN;
+  Turn a, b, c;
+  load(t_first, a);
+  load(t_first + STRIDE, b);
+  for (int t0 = t_first; t0 < end; t0 += 3 * STRIDE) {
+    load(t0 + 2 * STRIDE, c);
+    compute(a);
+    load(t0 + 3 * STRIDE, a);
+    compute(b);  // zeros past the end
+    load(t0 + 4 * STRIDE, b);
+    compute(c);
+  }
+  // Sum of the waves: halves added onto each other, in wave order.
+#pragma unroll
+  for (int h = kF64Waves / 2; h >= 1; h /= 2) {
+    if (wave >= h && wave < 2 * h) {
+#pragma unroll
+      for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) red[((wave - h) * NP + p) * 256 + 64 * i + lane] = acc[p][i];
+    }
+    __syncthreads();
+    if (wave < h) {
+#pragma unroll
+      for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[p][i] += red[(wave * NP + p) * 256 + 64 * i + lane];
+    }
+    __syncthreads();
+  }
+  if (wave == 0) {
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int I = p <= JA ? p : p - JA - 1, J = p <= JA ? JA : JB;
+      const int pr = I * NB - (I * (I - 1)) / 2 + (J - I);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) out[pr * 256 + 64 * i + lane] = acc[p][i];
+    }
+  }
+}
+
+template <typename T, int D, bool MARKED>
+__global__ __launch_bounds__(kF64Threads, sizeof(T) == 2 ? 4 : 2) void gram_f64_kernel(
     Geo g, const T* __restrict__ v, const float* __restrict__ wbuf,
-    const uint32_t* __restrict__ uflags, double* __restrict__ partials, int pchunks, int pchunk,
-    int items) {
-  constexpr int R = D / 16;
+    const uint32_t* __restrict__ rcount, const int32_t* __restrict__ rlist,
+    double* __restrict__ partials, int pchunks, int pchunk, int pslots) {
   constexpr int NB = D / 16;
   constexpr int NPAIR = NB * (NB + 1) / 2;
-  __shared__ float vs[32][D];
-  __shared__ double ws[32];
-  if constexpr (REFINE_ONLY) {
-    // The flags of all the walk's items at once (a load per thread, not one
-    // per item in turn): a workgroup with no marked unit ends here.
-    bool any = false;
-    for (int item = blockIdx.x + threadIdx.x * gridDim.x; item < items;
-         item += gridDim.x * kThreads) {
-      int u, chunk;
-      any |= grid_unit_chunk_at<true>(g, pchunks, item, u, chunk) && (uflags[u] & kUnitRefine);
-    }
-    if (!__syncthreads_or(any)) return;
+  constexpr int NCP = NB / 2;
+  __shared__ double red[kF64Waves / 2 * (NB + 1) * 256];
+  int nu = g.U, nch = pchunks, tok = pchunk;
+  if constexpr (MARKED) {
+    nu = (int)*rcount;
+    if (nu == 0) return;
+    const RefineCut rc = refine_cut(nu, g.maxn, pslots);
+    nch = rc.nch;
+    tok = rc.tok;
   }
-  // one (unit, chunk) item per workgroup, or (REFINE_ONLY) a grid-stride walk
-  for (int item = blockIdx.x; item < items; item += gridDim.x) {
-  int u, chunk;
-  if (!grid_unit_chunk_at<true>(g, pchunks, item, u, chunk)) continue;
-  if (REFINE_ONLY && !(uflags[u] & kUnitRefine)) continue;
-  const Unit un = decode_unit(g, u);
-  const int base = chunk * pchunk;
-  if (base >= un.n) continue;
-  const int tid = threadIdx.x, ty = tid / 16, tx = tid % 16;
-  const T* vb = v + un.l * g.vsl + un.h * g.vsh;
-  const int64_t trow = token_row(g, un);
-  const int end = min(un.n, base + pchunk);
-  double acc[R][R];
-#pragma unroll
-  for (int a = 0; a < R; ++a)
-#pragma unroll
-    for (int b = 0; b < R; ++b) acc[a][b] = 0.0;
-  for (int t0 = base; t0 < end; t0 += 32) {
-    __syncthreads();
-    for (int e = tid; e < 32 * D; e += kThreads) {
-      const int tok = e / D, c = e % D;
-      vs[tok][c] = (t0 + tok < end) ? to_f32(vb[(un.t0 + t0 + tok) * g.vst + c]) : 0.0f;
+  // (unit, chunk) pairs in groups of 8; the NCP items of a pair 8 apart
+  const int64_t pairs = (int64_t)nu * nch;
+  const int64_t items = (pairs + 7) / 8 * 8 * NCP;
+  for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
+    const int r = (int)(item % (8 * NCP)), cp = r >> 3;
+    const int64_t pair = item / (8 * NCP) * 8 + (r & 7);
+    if (pair >= pairs) continue;
+    const int li = (int)(pair / nch), chunk = (int)(pair % nch);
+    const int u = MARKED ? rlist[li] : li;
+    const Unit un = decode_unit(g, u);
+    const int base = chunk * tok;
+    if (base >= un.n) continue;
+    const int end = min(un.n, base + tok);
+    const T* vb = v + un.l * g.vsl + un.h * g.vsh + un.t0 * g.vst;
+    const float* wrow = wbuf + token_row(g, un);
+    double* out = partials + pair * (NPAIR * 256);
+    if constexpr (NCP == 4) {
+      switch (cp) {
+        case 0: gram_f64_item<T, D, 0>(vb, g.vst, wrow, base, end, out, red); break;
+        case 1: gram_f64_item<T, D, 1>(vb, g.vst, wrow, base, end, out, red); break;
+        case 2: gram_f64_item<T, D, 2>(vb, g.vst, wrow, base, end, out, red); break;
+        default: gram_f64_item<T, D, 3>(vb, g.vst, wrow, base, end, out, red); break;
+      }
+    } else {
+      if (cp == 0) gram_f64_item<T, D, 0>(vb, g.vst, wrow, base, end, out, red);
+      else gram_f64_item<T, D, 1>(vb, g.vst, wrow, base, end, out, red);
     }
-    if (tid < 32) {
-      const int t = t0 + tid;
-      ws[tid] = (t < end) ? (double)wbuf[trow + t] : 0.0;
-    }
-    __syncthreads();
-    for (int tok = 0; tok < 32; ++tok) {
-      const double w = ws[tok];
-      double xa[R], vb2[R];
-#pragma unroll
-      for (int a = 0; a < R; ++a) xa[a] = w * (double)vs[tok][ty * R + a];
-#pragma unroll
-      for (int b = 0; b < R; ++b) vb2[b] = (double)vs[tok][tx * R + b];
-#pragma unroll
-      for (int a = 0; a < R; ++a)
-#pragma unroll
-        for (int b = 0; b < R; ++b) acc[a][b] += xa[a] * vb2[b];
-    }
-  }
-  double* out = partials + ((int64_t)u * pchunks + chunk) * (NPAIR * 256);
-#pragma unroll
-  for (int a = 0; a < R; ++a)
-#pragma unroll
-    for (int b = 0; b < R; ++b) {
-      const int row = ty * R + a, col = tx * R + b;
-      const int i = row / 16, j = col / 16;
-      if (i > j) continue;
-      const int p = i * NB - (i * (i - 1)) / 2 + (j - i);
-      const int ln = ((row % 16) / 4) * 16 + (col % 16);
-      out[p * 256 + ln * 4 + (row % 4)] = acc[a][b];
-    }
-  __syncthreads();  // the staged tokens of this item are read before the next item's
   }
 }
 
@@ -415,19 +500,20 @@ hipError_t launch_gram(const Launch& L, const void* v, bool refine) {
   }
   if (!L.ws.mfma && refine) return hipSuccess;
   // fp64: all units of fp32 inputs, or the marked units of bf16 inputs
-  const int64_t items = chunked_grid(g, L.ws.pchunks);
-  const dim3 grid((unsigned)(L.ws.mfma ? std::min<int64_t>(items, kRefineBlocks) : items));
-  double* part = ws_ptr<double>(L.wsp, L.ws.gram);
+  const int64_t items = ((int64_t)g.U * L.ws.pchunks + 7) / 8 * 8 * (g.D / 32);
+  const unsigned blocks = (unsigned)std::min<int64_t>(items, L.ws.mfma ? kRefineBlocks : kF64Blocks);
+  if (blocks == 0) return hipSuccess;
   auto go = [&](auto kern, auto vv) {
-    kern<<<grid, kThreads, 0, L.stream>>>(g, vv, wb, uf, part, L.ws.pchunks, L.ws.pchunk,
-                                          (int)items);
+    kern<<<blocks, kF64Threads, 0, L.stream>>>(
+        g, vv, wb, ws_ptr<uint32_t>(L.wsp, L.ws.status) + 1, ws_ptr<int32_t>(L.wsp, L.ws.rlist),
+        ws_ptr<double>(L.wsp, L.ws.gram), L.ws.pchunks, L.ws.pchunk, L.ws.pslots);
   };
   if (L.ws.mfma) {
-    if (g.D == 128) go(gram_precise_kernel<uint16_t, 128, true>, (const uint16_t*)v);
-    else go(gram_precise_kernel<uint16_t, 64, true>, (const uint16_t*)v);
+    if (g.D == 128) go(gram_f64_kernel<uint16_t, 128, true>, (const uint16_t*)v);
+    else go(gram_f64_kernel<uint16_t, 64, true>, (const uint16_t*)v);
   } else {
-    if (g.D == 128) go(gram_precise_kernel<float, 128, false>, (const float*)v);
-    else go(gram_precise_kernel<float, 64, false>, (const float*)v);
+    if (g.D == 128) go(gram_f64_kernel<float, 128, false>, (const float*)v);
+    else go(gram_f64_kernel<float, 64, false>, (const float*)v);
   }
   return hipGetLastError();
 }

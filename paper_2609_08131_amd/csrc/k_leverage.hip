@@ -9,8 +9,7 @@
 // lanes that share a token.
 //
 // fp64 pass (every unit of fp32 inputs; the units of bf16 inputs that the
-// factorisation sent to the fp64 path): fp64 VALU, L^{-1} in LDS, 8 threads
-// per token.
+// factorisation sent to the fp64 path): the same product on the fp64 MFMA.
 #include <algorithm>
 
 #include "jacap_internal.hpp"
@@ -156,88 +155,140 @@ __global__ __launch_bounds__(kThreads, 2) void leverage_mfma_kernel(
   }
 }
 
-// fp64 leverage: every unit (fp32 inputs), or only the units marked
-// kUnitRefine (REFINE_ONLY, bf16 inputs). L^{-1} comes from the reduced-Gram
-// buffer in the lower-block layout written by the fp64 factorisation.
-template <typename T, int D, bool REFINE_ONLY>
-__global__ __launch_bounds__(kThreads) void leverage_precise_kernel(
+// ---------------------------------------------------------------------------
+// fp64 leverage: every unit (fp32 inputs), or (MARKED) the marked units of bf16
+// inputs, from their list. Y = L^{-1} V^T on the fp64 MFMA 16x16x4: rows are 16
+// channels of a block J of L^{-1}, columns 16 tokens, and only the blocks
+// B <= J of the lower triangle are multiplied.
+//
+// Bound by the fp64 matrix rate (144 MFMAs of 64 cycles per 16 tokens at
+// d = 128). L^{-1} lies in LDS in the operand order of store_lower_f64 (72 KB:
+// two workgroups per compute unit), two K-steps per conflict-free 16-byte read;
+// each wave runs two tiles of 16 tokens against every value read, which
+// halves the reads and gives two independent accumulation chains. V goes
+// straight from global memory into the operand: K-step s of a 16-channel block
+// takes lane (token r, q)'s channel 4 q + s of the block, so a lane reads four
+// consecutive channels of its token; the next tiles are read a trip ahead.
+//
+// Measured (MI355X): 241 marked units of 8192 tokens, d = 128, bf16: 8.85 ms
+// with eight threads per token on the fp64 VALU, both operands from LDS,
+// 0.63 ms here (0.54 ms at the measured fp64 matrix rate of 72 TFLOP/s);
+// 14 marked units of 2176 tokens among 4096: 2036 us and 23 us.
+// ---------------------------------------------------------------------------
+template <typename T, int D, bool MARKED>
+__global__ __launch_bounds__(kThreads, 2) void leverage_f64_kernel(
     Geo g, const T* __restrict__ v, const float* __restrict__ wbuf,
     const double* __restrict__ xred, const uint32_t* __restrict__ uflags,
-    float* __restrict__ scores, int lchunks, int lchunk, int items) {
-  constexpr int LD = D + 1;
+    const uint32_t* __restrict__ rcount, const int32_t* __restrict__ rlist,
+    float* __restrict__ scores, int lchunks, int lchunk) {
   constexpr int NB = D / 16;
   constexpr int NPAIR = NB * (NB + 1) / 2;
-  constexpr int TPT = 8;                 // threads per token
-  constexpr int TOK = kThreads / TPT;    // tokens per tile
-  __shared__ double X[D * LD];
-  __shared__ float vs[TOK][D + 1];  // padded: the wave's 8 token rows in distinct banks
-  if constexpr (REFINE_ONLY) {
-    // The flags of all the walk's items at once (a load per thread, not one
-    // per item in turn): a workgroup with no marked unit ends here.
-    bool any = false;
-    for (int item = blockIdx.x + threadIdx.x * gridDim.x; item < items;
-         item += gridDim.x * kThreads) {
-      int u, chunk;
-      any |= grid_unit_chunk_at<true>(g, lchunks, item, u, chunk) && (uflags[u] & kUnitRefine);
+  constexpr int TT = 2;                        // 16-token tiles per wave
+  constexpr int TRIP = TT * 16 * (kThreads / 64);  // tokens per workgroup trip
+  constexpr int WORDS = 4 * sizeof(T) / 4;     // 32-bit words of four channels
+  // fp32 tiles are read where they are used: a second set of them would spill
+  constexpr bool AHEAD = sizeof(T) == 2;
+  static_assert(TRIP == kLChunkPreciseMin, "the smallest chunk is one trip");
+  __shared__ __attribute__((aligned(16))) double X[NPAIR * 256];
+  int nu = g.U, nch = lchunks, tok = lchunk;
+  if constexpr (MARKED) {
+    nu = (int)*rcount;
+    if (nu == 0) return;
+    // about kLRefineItems items, in whole trips
+    nch = min(max(kLRefineItems / nu, 1), (g.maxn + TRIP - 1) / TRIP);
+    tok = ((g.maxn + nch - 1) / nch + TRIP - 1) / TRIP * TRIP;
+    nch = (g.maxn + tok - 1) / tok;
+  }
+  const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, q4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t items = (int64_t)nu * nch;
+  for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
+    const int li = (int)(item / nch), chunk = (int)(item % nch);
+    const int u = MARKED ? rlist[li] : li;
+    const Unit un = decode_unit(g, u);
+    const int base = chunk * tok;
+    if (base >= un.n) continue;
+    const int end = min(un.n, base + tok);
+    const int64_t trow = token_row(g, un);
+    if (uflags[u] & kUnitFailed) {  // non-finite input or singular A: NaN scores
+      for (int t = base + tid; t < end; t += kThreads) scores[trow + t] = __builtin_nanf("");
+      continue;
     }
-    if (!__syncthreads_or(any)) return;
-  }
-  // one (unit, chunk) item per workgroup, or (REFINE_ONLY) a grid-stride walk
-  for (int item = blockIdx.x; item < items; item += gridDim.x) {
-  int u, chunk;
-  if (!grid_unit_chunk_at<true>(g, lchunks, item, u, chunk)) continue;
-  const uint32_t uf = uflags[u];
-  if (REFINE_ONLY && !(uf & kUnitRefine)) continue;
-  const Unit un = decode_unit(g, u);
-  const int base = chunk * lchunk;
-  if (base >= un.n) continue;
-  const int tid = threadIdx.x;
-  const int64_t trow = token_row(g, un);
-  const int end = min(un.n, base + lchunk);
-  if (uf & kUnitFailed) {  // non-finite input or singular A: NaN scores
-    for (int t = base + tid; t < end; t += kThreads) scores[trow + t] = __builtin_nanf("");
-    continue;
-  }
-  __syncthreads();  // the previous item's X and staged tokens are no longer read
-  // lower blocks of L^{-1}: pair p = (bi <= bj) holds X[16 bj + r][16 bi + c]
-  const double* Xb = xred + (int64_t)u * (NPAIR * 256);
-  for (int e = tid; e < NPAIR * 256; e += kThreads) {
-    int p = e >> 8, bi = 0;
+    const T* vb = v + un.l * g.vsl + un.h * g.vsh + un.t0 * g.vst;
+    const int32_t vstb = (int32_t)g.vst * (int32_t)sizeof(T);
+    const int32_t voff = r16 * vstb + q4 * (int32_t)(4 * sizeof(T));
+    struct Tiles { uint32_t v[TT][NB][WORDS]; float w[TT]; };
+    // Rows past the chunk's end load as zeros and are not stored.
+    auto load = [&](int t0, Tiles& tl) {
 #pragma unroll
-    for (int q = 0; q < NB; ++q)
-      if (p >= NB - bi) { p -= NB - bi; ++bi; }
-    const int bj = bi + p;
-    X[(16 * bj + ((e >> 4) & 15)) * LD + 16 * bi + (e & 15)] = Xb[e];
-  }
-  const T* vb = v + un.l * g.vsl + un.h * g.vsh;
-  const int my_tok = tid / TPT, sub = tid % TPT;
-  for (int t0 = base; t0 < end; t0 += TOK) {
-    __syncthreads();
-    for (int e = tid; e < TOK * D; e += kThreads) {
-      const int tk = e / D, c = e % D;
-      vs[tk][c] = (t0 + tk < end) ? to_f32(vb[(un.t0 + t0 + tk) * g.vst + c]) : 0.0f;
-    }
-    __syncthreads();
-    double ss = 0.0;
-    for (int a = sub; a < D; a += TPT) {
-      // four independent chains over b (latency, not order, bounds this loop)
-      double y4[4] = {0.0, 0.0, 0.0, 0.0};
-      int b = 0;
-      for (; b + 3 <= a; b += 4) {
+      for (int tt = 0; tt < TT; ++tt) {
+        const int ts = t0 + 16 * tt;
+        const int32_t rows = min(end - ts, 16);
+        const auto vr = buffer_range(vb + (int64_t)ts * g.vst,
+                                     rows_bytes(rows, vstb, D * (int32_t)sizeof(T)));
 #pragma unroll
-        for (int q = 0; q < 4; ++q) y4[q] = fma(X[a * LD + b + q], (double)vs[my_tok][b + q], y4[q]);
+        for (int B = 0; B < NB; ++B)
+          buffer_load_words<WORDS>(vr, voff + B * (int32_t)(16 * sizeof(T)), tl.v[tt][B]);
+        tl.w[tt] = buffer_load_f32(buffer_range(wbuf + trow + ts, max(rows, 0) * 4), r16 * 4);
       }
-      for (; b <= a; ++b) y4[0] = fma(X[a * LD + b], (double)vs[my_tok][b], y4[0]);
-      const double y = (y4[0] + y4[1]) + (y4[2] + y4[3]);
-      ss += y * y;
+      __builtin_amdgcn_sched_barrier(0);  // issued here, a trip ahead of their use
+    };
+    const int t_first = base + wave * TT * 16;
+    Tiles nxt;
+    if constexpr (AHEAD) load(t_first, nxt);
+    __syncthreads();  // the previous item's X is no longer read
+    {
+      const double2* src = reinterpret_cast<const double2*>(xred + (int64_t)u * (NPAIR * 256));
+      double2* dst = reinterpret_cast<double2*>(X);
+      for (int e = tid; e < NPAIR * 128; e += kThreads) dst[e] = src[e];
     }
+    __syncthreads();
+    for (int t0 = t_first; t0 < end; t0 += TRIP) {
+      double x[TT][NB][4];
+      float w[TT];
+      if constexpr (!AHEAD) load(t0, nxt);
 #pragma unroll
-    for (int o = 1; o < TPT; o <<= 1) ss += __shfl_xor(ss, o);
-    const int t = t0 + my_tok;
-    if (sub == 0 && t < end) {
-      scores[trow + t] = (float)((double)wbuf[trow + t] * ss);
+      for (int tt = 0; tt < TT; ++tt) {
+        w[tt] = nxt.w[tt];
+#pragma unroll
+        for (int B = 0; B < NB; ++B)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) x[tt][B][s] = word_elem<T, WORDS>(nxt.v[tt][B], s);
+      }
+      if constexpr (AHEAD) load(t0 + TRIP, nxt);  // empty past the chunk's end
+      double ss[TT];
+#pragma unroll
+      for (int tt = 0; tt < TT; ++tt) ss[tt] = 0.0;
+#pragma unroll
+      for (int J = 0; J < NB; ++J) {
+        f64x4 y[TT];
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) y[tt] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int B = 0; B <= J; ++B) {
+          const double2* xp =
+              reinterpret_cast<const double2*>(X + (J * (J + 1) / 2 + B) * 256) + lane;
+          const double2 x0 = xp[0], x1 = xp[64];  // K-steps 0, 1 and 2, 3
+          const double a[4] = {x0.x, x0.y, x1.x, x1.y};
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt) y[tt] = mfma64(a[s], x[tt][B][s], y[tt]);
+        }
+        // y[i]: channel 16 J + 4 i + q4 of token r16
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) ss[tt] = fma(y[tt][i], y[tt][i], ss[tt]);
+      }
+#pragma unroll
+      for (int tt = 0; tt < TT; ++tt) {
+        ss[tt] += __shfl_xor(ss[tt], 16);
+        ss[tt] += __shfl_xor(ss[tt], 32);
+        const int t = t0 + 16 * tt + r16;
+        if (q4 == 0 && t < end) scores[trow + t] = (float)((double)w[tt] * ss[tt]);
+      }
     }
-  }
   }
 }
 
@@ -268,21 +319,22 @@ hipError_t launch_leverage(const Launch& L, const void* v, float* scores) {
 // fp64 leverage: every unit of fp32 inputs, or the marked units of bf16 inputs.
 hipError_t launch_leverage_precise(const Launch& L, const void* v, float* scores) {
   const Geo& g = L.geo;
-  const int64_t items = chunked_grid(g, L.ws.plchunks);
-  const dim3 grid((unsigned)(L.ws.mfma ? std::min<int64_t>(items, kRefineBlocks) : items));
-  const float* wb = ws_ptr<float>(L.wsp, L.ws.wgt);
-  const uint32_t* uf = ws_ptr<uint32_t>(L.wsp, L.ws.uflags);
-  const double* xr = ws_ptr<double>(L.wsp, L.ws.gram_red);
+  const int64_t items = (int64_t)g.U * L.ws.plchunks;
+  const unsigned blocks =
+      (unsigned)std::min<int64_t>(items, L.ws.mfma ? kRefineBlocks : (int64_t(1) << 20));
+  if (blocks == 0) return hipSuccess;
   auto go = [&](auto kern, auto vv) {
-    kern<<<grid, kThreads, 0, L.stream>>>(g, vv, wb, xr, uf, scores, L.ws.plchunks, L.ws.plchunk,
-                                          (int)items);
+    kern<<<blocks, kThreads, 0, L.stream>>>(
+        g, vv, ws_ptr<float>(L.wsp, L.ws.wgt), ws_ptr<double>(L.wsp, L.ws.gram_red),
+        ws_ptr<uint32_t>(L.wsp, L.ws.uflags), ws_ptr<uint32_t>(L.wsp, L.ws.status) + 1,
+        ws_ptr<int32_t>(L.wsp, L.ws.rlist), scores, L.ws.plchunks, L.ws.plchunk);
   };
   if (L.ws.mfma) {
-    if (g.D == 128) go(leverage_precise_kernel<uint16_t, 128, true>, (const uint16_t*)v);
-    else go(leverage_precise_kernel<uint16_t, 64, true>, (const uint16_t*)v);
+    if (g.D == 128) go(leverage_f64_kernel<uint16_t, 128, true>, (const uint16_t*)v);
+    else go(leverage_f64_kernel<uint16_t, 64, true>, (const uint16_t*)v);
   } else {
-    if (g.D == 128) go(leverage_precise_kernel<float, 128, false>, (const float*)v);
-    else go(leverage_precise_kernel<float, 64, false>, (const float*)v);
+    if (g.D == 128) go(leverage_f64_kernel<float, 128, false>, (const float*)v);
+    else go(leverage_f64_kernel<float, 64, false>, (const float*)v);
   }
   return hipGetLastError();
 }

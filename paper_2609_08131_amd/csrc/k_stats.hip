@@ -8,11 +8,12 @@
 
 namespace jacap {
 
-// Clears the sticky status word and the per-unit flags. A fill kernel rather
-// than hipMemsetAsync so that the launch sequence can be captured in a graph.
+// Clears the sticky status word, the marked units' count after it and the
+// per-unit flags. A fill kernel rather than hipMemsetAsync so that the launch
+// sequence can be captured in a graph.
 __global__ void init_kernel(uint32_t* __restrict__ status, uint32_t* __restrict__ uflags, int U) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0) status[0] = 0u;
+  if (i < 2) status[i] = 0u;
   if (i < U) uflags[i] = 0u;
 }
 
@@ -986,12 +987,12 @@ hipError_t launch_kpass(const Launch& L, const void* k, const void* q) {
 // Z = sum_c Z_c exp(m_c - m) (fp64, fixed order), then the Eq. 8 importance
 // weight of every token of the block's chunk (fp64, stored as fp32).
 // wchunks blocks per unit. Every block of a unit merges the chunk statistics
-// in the same order, so all of them use bit-identical (m, Z); block 0 stores them.
+// in the same order, so all of them use bit-identical (m, Z).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kThreads) void softmax_weights_kernel(
     Geo g, const float2* __restrict__ cstat, int kchunks, const float* __restrict__ zbuf,
-    const float* __restrict__ kbuf, double inv_d, int wchunks, float* __restrict__ m_out,
-    double* __restrict__ z_out, double* __restrict__ scale_out, float* __restrict__ wout) {
+    const float* __restrict__ kbuf, double inv_d, int wchunks, double* __restrict__ scale_out,
+    float* __restrict__ wout) {
   int u, chunk;
   if (!grid_unit_chunk<false>(g, wchunks, u, chunk)) return;
   const int tid = threadIdx.x;
@@ -1000,7 +1001,7 @@ __global__ __launch_bounds__(kThreads) void softmax_weights_kernel(
   __shared__ int redi[kThreads / 64];
   __shared__ double redd[kThreads / 64];
   if (un.n == 0) {
-    if (chunk == 0 && tid == 0) { m_out[u] = 0.0f; z_out[u] = 1.0; scale_out[u] = 1.0; }
+    if (chunk == 0 && tid == 0) scale_out[u] = 1.0;
     return;
   }
   const int base = chunk * kWChunk;
@@ -1030,7 +1031,7 @@ __global__ __launch_bounds__(kThreads) void softmax_weights_kernel(
   // factorisation, which leaves every score w_i v_i^T A^{-1} v_i unchanged.
   const double rho_max = fmin(0.25, rest / s);
   const double wscale = rho_max > 0.0 && rho_max < 0x1p-20 ? ldexp(1.0, -2 * ilogb(rho_max)) : 1.0;
-  if (chunk == 0 && tid == 0) { m_out[u] = m; z_out[u] = s; scale_out[u] = wscale; }
+  if (chunk == 0 && tid == 0) scale_out[u] = wscale;
   const double wfac = wscale * inv_d;
   const int64_t trow = token_row(g, un);
   const int end = min(un.n, base + kWChunk);
@@ -1069,9 +1070,7 @@ hipError_t launch_softmax_weights(const Launch& L) {
   softmax_weights_kernel<<<grid, kThreads, 0, L.stream>>>(
       L.geo, ws_ptr<float2>(L.wsp, L.ws.cstat), L.ws.kchunks, ws_ptr<float>(L.wsp, L.ws.z),
       ws_ptr<float>(L.wsp, L.ws.kappa), 1.0 / (double)L.geo.D, wchunks,
-      ws_ptr<float>(L.wsp, L.ws.smax_m),
-      ws_ptr<double>(L.wsp, L.ws.smax_z), ws_ptr<double>(L.wsp, L.ws.wscale),
-      ws_ptr<float>(L.wsp, L.ws.wgt));
+      ws_ptr<double>(L.wsp, L.ws.wscale), ws_ptr<float>(L.wsp, L.ws.wgt));
   return hipGetLastError();
 }
 
