@@ -14,6 +14,8 @@ namespace jacap {
 // ---------------------------------------------------------------------------
 constexpr int kThreads = 256;        // 4 wave64 per workgroup
 constexpr int kKChunk = 1024;        // tokens per workgroup in the K pass
+constexpr int kKChunkMin = 256;      // ... of batches that would not fill the chip (DIAG)
+constexpr int kSmallBlocks = 2 * 256; // fewer workgroups than this leave compute units idle
 constexpr int kFullMaxQ = 256;       // window queries the FULL-covariance MFMA K pass stages
 // FULL covariance: units of at least this many tokens take kappa from the
 // triangular factor of Lambda_Q (a fixed per-unit cost that long units repay).
@@ -32,7 +34,8 @@ constexpr int kLevMinBlocks = 2048;  // leverage chunks shrink until the grid ha
 constexpr int kLChunkPrecise = 1024; // tokens per workgroup in the fp64 leverage pass (fp32 keys):
 constexpr int kLChunkPreciseMin = 128; // ... at most, and at least (small batches; one workgroup trip)
 constexpr int kLRefineItems = 2048;  // the marked bf16 units are cut into about this many chunks
-constexpr int kWChunk = 4096;        // tokens per workgroup in the weight pass
+constexpr int kWChunk = 4096;        // tokens per workgroup in the weight pass: at most,
+constexpr int kWChunkMin = 1024;     // ... and at least (batches that would not fill the chip)
 // The K pass sums a chunk's exp(z - max) terms (all but the max's own) as
 // exp(z - max + kRestShift) in fp32, so that they stay normal down to
 // z - max ~ -150 (a sharply peaked softmax at small temperature).
@@ -194,7 +197,7 @@ struct Workspace {
   size_t gst;      // int32  [L][H][T]       greedy: picks made at that time (-1 = taken)
   size_t gent;     // GreedyEntry [U][ceil(maxn / 256)]  greedy: best of each 256-position block
   size_t total;
-  int kchunks, wchunks, gchunks, gchunk, gparts, lchunks, lchunk;
+  int kchunks, kchunk, wchunks, wchunk, gchunks, gchunk, gparts, lchunks, lchunk;
   int pchunks, pchunk;  // chunks of the fp64 Gram pass over every unit (fp32 inputs)
   int pslots;           // fp64 partials the Gram buffer holds
   int plchunks, plchunk;  // chunks of the fp64 leverage pass over every unit

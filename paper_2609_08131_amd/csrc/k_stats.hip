@@ -53,12 +53,22 @@ hipError_t launch_head_mean(const Launch& L, const float* hs, float* scores) {
 // ---------------------------------------------------------------------------
 // mu_Q and Lambda_Q of the pooled window (G query heads x w positions):
 // sample mean and 1/N covariance, accumulated in fp64 in a fixed order.
+//
+// A unit's workgroup is a chain of memory latency and two reductions, so what
+// counts is how many workgroups a compute unit holds and that the window is
+// read once: each thread keeps its first HELD row pieces in registers for
+// the second pass (all requested before the first is used), and the diagonal
+// statistics, which every path takes, are compiled apart from the full matrix
+// (FULL), whose accumulators and staged rows limit a compute unit to three
+// workgroups. Measured (MI355X): 4096 units of 256 x 128 bf16 queries 155 us with
+// both in one kernel and the window read twice, 76 us here; 8 units of 128
+// queries 8.7 and 6.1 us.
 // ---------------------------------------------------------------------------
-template <typename T, int D>
+template <typename T, int D, bool FULL>
 __global__ __launch_bounds__(kThreads) void qstats_kernel(Geo g, const T* __restrict__ q,
                                                           double* __restrict__ mu_out,
                                                           double* __restrict__ lam_out,
-                                                          float* __restrict__ lamfull, int full,
+                                                          float* __restrict__ lamfull,
                                                           uint32_t* status, uint32_t* uflags) {
   const int u = blockIdx.x;
   const int tid = threadIdx.x;
@@ -76,12 +86,34 @@ __global__ __launch_bounds__(kThreads) void qstats_kernel(Geo g, const T* __rest
   const int cl = tid % CL, rp = tid / CL;
   __shared__ double smu[D];
   __shared__ double part[RP][D];
-  auto row_piece = [&](int r, double (&x)[VEC]) {
+  constexpr int HELD = 8;
+  auto row_raw = [&](int r) {
     const int gq = r / g.w, p = r - gq * g.w;
-    const uint4 raw = *reinterpret_cast<const uint4*>(qb + gq * g.qsh + p * g.qsp + cl * VEC);
+    return *reinterpret_cast<const uint4*>(qb + gq * g.qsh + p * g.qsp + cl * VEC);
+  };
+  auto unpack = [&](const uint4& raw, double (&x)[VEC]) {
     const T* xv = reinterpret_cast<const T*>(&raw);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) x[e] = (double)to_f32(xv[e]);
+  };
+  uint4 held[HELD];
+#pragma unroll
+  for (int i = 0; i < HELD; ++i) held[i] = row_raw(min(rp + i * RP, Ns - 1));
+  // f(x) on this thread's rows rp, rp + RP, ... in order
+  auto each_row = [&](auto f) {
+#pragma unroll
+    for (int i = 0; i < HELD; ++i)
+      if (rp + i * RP < Ns) {
+        double x[VEC];
+        unpack(held[i], x);
+        f(x);
+      }
+#pragma unroll 4
+    for (int r = rp + HELD * RP; r < Ns; r += RP) {
+      double x[VEC];
+      unpack(row_raw(r), x);
+      f(x);
+    }
   };
   auto combine = [&](const double (&acc)[VEC], double* out) {
 #pragma unroll
@@ -97,22 +129,18 @@ __global__ __launch_bounds__(kThreads) void qstats_kernel(Geo g, const T* __rest
   double acc[VEC];
 #pragma unroll
   for (int e = 0; e < VEC; ++e) acc[e] = 0.0;
-  for (int r = rp; r < Ns; r += RP) {
-    double x[VEC];
-    row_piece(r, x);
+  each_row([&](const double (&x)[VEC]) {
 #pragma unroll
     for (int e = 0; e < VEC; ++e) acc[e] += x[e];
-  }
+  });
   combine(acc, smu);
   double m[VEC];
 #pragma unroll
   for (int e = 0; e < VEC; ++e) { m[e] = smu[cl * VEC + e]; acc[e] = 0.0; }
-  for (int r = rp; r < Ns; r += RP) {
-    double x[VEC];
-    row_piece(r, x);
+  each_row([&](const double (&x)[VEC]) {
 #pragma unroll
     for (int e = 0; e < VEC; ++e) acc[e] += (x[e] - m[e]) * (x[e] - m[e]);
-  }
+  });
   __shared__ double svar[D];
   combine(acc, svar);
   if (tid < D) {
@@ -121,11 +149,11 @@ __global__ __launch_bounds__(kThreads) void qstats_kernel(Geo g, const T* __rest
     lam_out[(int64_t)u * D + tid] = v;
     if (!isfinite(mm) || !isfinite(v)) raise_flags(status, uflags, u, kUnitNonfinite);
   }
-  if (!full) return;
+  if constexpr (!FULL) return;
   // Full covariance: each thread owns D*D/kThreads entries; rows are staged,
   // centred, 32 at a time in LDS.
   constexpr int PER = D * D / kThreads;
-  __shared__ double qt[32][D];
+  __shared__ double qt[FULL ? 32 : 1][D];
   double cacc[PER];
 #pragma unroll
   for (int k = 0; k < PER; ++k) cacc[k] = 0.0;
@@ -166,16 +194,16 @@ hipError_t launch_qstats(const Launch& L, const void* q) {
   uint32_t* st = ws_ptr<uint32_t>(L.wsp, L.ws.status);
   uint32_t* uf = ws_ptr<uint32_t>(L.wsp, L.ws.uflags);
   const bool bf = L.cfg->dtype == JACAP_DTYPE_BF16;
+  auto go = [&](auto diag, auto fullk, auto qp) {
+    if (full) fullk<<<g.U, kThreads, 0, L.stream>>>(g, qp, mu, lam, lf, st, uf);
+    else diag<<<g.U, kThreads, 0, L.stream>>>(g, qp, mu, lam, lf, st, uf);
+  };
   if (g.D == 128) {
-    if (bf)
-      qstats_kernel<uint16_t, 128><<<g.U, kThreads, 0, L.stream>>>(g, (const uint16_t*)q, mu, lam, lf, full, st, uf);
-    else
-      qstats_kernel<float, 128><<<g.U, kThreads, 0, L.stream>>>(g, (const float*)q, mu, lam, lf, full, st, uf);
+    if (bf) go(qstats_kernel<uint16_t, 128, false>, qstats_kernel<uint16_t, 128, true>, (const uint16_t*)q);
+    else go(qstats_kernel<float, 128, false>, qstats_kernel<float, 128, true>, (const float*)q);
   } else {
-    if (bf)
-      qstats_kernel<uint16_t, 64><<<g.U, kThreads, 0, L.stream>>>(g, (const uint16_t*)q, mu, lam, lf, full, st, uf);
-    else
-      qstats_kernel<float, 64><<<g.U, kThreads, 0, L.stream>>>(g, (const float*)q, mu, lam, lf, full, st, uf);
+    if (bf) go(qstats_kernel<uint16_t, 64, false>, qstats_kernel<uint16_t, 64, true>, (const uint16_t*)q);
+    else go(qstats_kernel<float, 64, false>, qstats_kernel<float, 64, true>, (const float*)q);
   }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || !full_kpass_tri(L, q)) return e;
@@ -252,6 +280,7 @@ __device__ __forceinline__ F group_sum(F v) {
 // own relative precision when one token dominates the softmax, which
 // 1 - alpha of that token needs (it is the rest of Z over Z); the shift keeps
 // its terms out of fp32's subnormal range.
+template <int KC>
 __device__ __forceinline__ void kpass_epilogue(const Unit& un, int u, int base, int64_t trow,
                                                const float* zsh, const float* ksq, float* red,
                                                float* __restrict__ zout,
@@ -261,7 +290,7 @@ __device__ __forceinline__ void kpass_epilogue(const Unit& un, int u, int base, 
   const int tid = threadIdx.x;
   __syncthreads();
   bool bad = false;
-  for (int tl = tid; tl < kKChunk; tl += kThreads) {
+  for (int tl = tid; tl < KC; tl += kThreads) {
     const int i = base + tl;
     if (i < un.n) {
       const float z = zsh[tl], kq = ksq[tl];
@@ -272,8 +301,8 @@ __device__ __forceinline__ void kpass_epilogue(const Unit& un, int u, int base, 
   }
   if (__any(bad) && (threadIdx.x & 63) == 0) raise_flags(status, uflags, u, kUnitNonfinite);
   __syncthreads();
-  static_assert(kKChunk % kThreads == 0, "whole logits per thread in the chunk reduction");
-  constexpr int ZPT = kKChunk / kThreads;
+  static_assert(KC % kThreads == 0, "whole logits per thread in the chunk reduction");
+  constexpr int ZPT = KC / kThreads;
   float zv[ZPT];
   float mloc = -INFINITY;
 #pragma unroll
@@ -282,7 +311,7 @@ __device__ __forceinline__ void kpass_epilogue(const Unit& un, int u, int base, 
     mloc = fmaxf(mloc, zv[q]);
   }
   const float m = block_combine(wave_max(mloc), red, [](float a, float b) { return fmaxf(a, b); });
-  int first = kKChunk;
+  int first = KC;
 #pragma unroll
   for (int q = ZPT - 1; q >= 0; --q)
     if (zv[q] == m) first = q * kThreads + tid;
@@ -299,10 +328,17 @@ __device__ __forceinline__ void kpass_epilogue(const Unit& un, int u, int base, 
 
 // ---------------------------------------------------------------------------
 // K pass: z_i = k_i . mu / (tau sqrt d) and kappa_i = k_i^T Lambda k_i for a
-// chunk of kKChunk tokens, then the chunk's (max z, sum exp(z - max)).
-// One 16-byte load per lane: a token row is spread over LPT lanes.
+// chunk of KC tokens, then the chunk's (max z, sum exp(z - max)).
+// One 16-byte load per lane: a token row is spread over LPT lanes. A chunk's
+// trips end with the unit's last token.
 // ---------------------------------------------------------------------------
-template <typename T, int D, bool FULL>
+// Logits of the trips that a chunk of n tokens does not run: -inf.
+template <int KC>
+__device__ __forceinline__ void kpass_fill(float* zsh, int done) {
+  for (int tl = done + threadIdx.x; tl < KC; tl += kThreads) zsh[tl] = -INFINITY;
+}
+
+template <typename T, int D, bool FULL, int KC>
 __global__ __launch_bounds__(kThreads) void kpass_kernel(
     Geo g, const T* __restrict__ k, const double* __restrict__ mu, const double* __restrict__ lam,
     const float* __restrict__ lamfull, float* __restrict__ zout, float* __restrict__ kout,
@@ -311,7 +347,7 @@ __global__ __launch_bounds__(kThreads) void kpass_kernel(
   int u, chunk;
   if (!grid_unit_chunk<false>(g, kchunks, u, chunk)) return;
   const Unit un = decode_unit(g, u);
-  const int base = chunk * kKChunk;
+  const int base = chunk * KC;
   if (base >= un.n) return;
 
   constexpr int VEC = 16 / sizeof(T);
@@ -331,8 +367,8 @@ __global__ __launch_bounds__(kThreads) void kpass_kernel(
   }
   drain_vmem();  // keep these prologue loads out of the loop's wait counts
 
-  __shared__ float zsh[kKChunk];
-  __shared__ float ksq[kKChunk];
+  __shared__ float zsh[KC];
+  __shared__ float ksq[KC];
   __shared__ float red[kThreads / 64];
   __shared__ float lamsh[FULL ? D * (D + 1) : 1];
   __shared__ float ksh[FULL ? TPB : 1][FULL ? D : 1];
@@ -347,7 +383,9 @@ __global__ __launch_bounds__(kThreads) void kpass_kernel(
   // UNR iterations per loop trip, their loads issued first (FULL mode keeps
   // one: it stages each token row in LDS between barriers).
   constexpr int UNR = FULL ? 1 : 4;
-  static_assert(kKChunk % (UNR * TPB) == 0, "chunk must be whole unrolled trips");
+  static_assert(KC % (UNR * TPB) == 0, "chunk must be whole unrolled trips");
+  const int lim = min(KC, (un.n - base + UNR * TPB - 1) / (UNR * TPB) * (UNR * TPB));
+  kpass_fill<KC>(zsh, lim);
   // Rows are loaded one trip ahead (double buffer); every load is
   // unconditional (past-the-end rows clamped, discarded) so the compiler's
   // wait counts stay static.
@@ -362,11 +400,11 @@ __global__ __launch_bounds__(kThreads) void kpass_kernel(
   };
   uint4 nxt[UNR];
   load_trip(0, nxt);
-  for (int it0 = 0; it0 < kKChunk; it0 += UNR * TPB) {
+  for (int it0 = 0; it0 < lim; it0 += UNR * TPB) {
     uint4 raw[UNR];
 #pragma unroll
     for (int j = 0; j < UNR; ++j) raw[j] = nxt[j];
-    load_trip(min(it0 + UNR * TPB, kKChunk - UNR * TPB), nxt);
+    load_trip(min(it0 + UNR * TPB, KC - UNR * TPB), nxt);
 #pragma unroll
     for (int j = 0; j < UNR; ++j) {
       const int tl = it0 + j * TPB + wave * TPW + tiw;
@@ -403,7 +441,7 @@ __global__ __launch_bounds__(kThreads) void kpass_kernel(
       }
     }
   }
-  kpass_epilogue(un, u, base, trow, zsh, ksq, red, zout, kout, cstat, kchunks, status, uflags,
+  kpass_epilogue<KC>(un, u, base, trow, zsh, ksq, red, zout, kout, cstat, kchunks, status, uflags,
                  chunk);
 }
 
@@ -411,7 +449,7 @@ __global__ __launch_bounds__(kThreads) void kpass_kernel(
 // reading D/32 16-byte pieces (the four lanes of a row read 64 contiguous
 // bytes per load), so a row's two sums need two quad DPP levels instead of
 // four row levels per 16-byte load.
-template <int D>
+template <int D, int KC>
 __global__ __launch_bounds__(kThreads) void kpass_quad_kernel(
     Geo g, const uint16_t* __restrict__ k, const double* __restrict__ mu,
     const double* __restrict__ lam, float* __restrict__ zout, float* __restrict__ kout,
@@ -420,7 +458,7 @@ __global__ __launch_bounds__(kThreads) void kpass_quad_kernel(
   int u, chunk;
   if (!grid_unit_chunk<false>(g, kchunks, u, chunk)) return;
   const Unit un = decode_unit(g, u);
-  const int base = chunk * kKChunk;
+  const int base = chunk * KC;
   if (base >= un.n) return;
 
   constexpr int VEC = 8;                 // bf16 per 16-byte piece
@@ -445,13 +483,13 @@ __global__ __launch_bounds__(kThreads) void kpass_quad_kernel(
     }
   drain_vmem();
 
-  __shared__ float zsh[kKChunk];
-  __shared__ float ksq[kKChunk];
+  __shared__ float zsh[KC];
+  __shared__ float ksq[KC];
   __shared__ float red[kThreads / 64];
 
   const uint16_t* kb = k + un.l * g.ksl + un.h * g.ksh + un.t0 * g.kst;
   const int64_t trow = token_row(g, un);
-  static_assert(kKChunk % (UNR * TPB) == 0, "chunk must be whole unrolled trips");
+  static_assert(KC % (UNR * TPB) == 0, "chunk must be whole unrolled trips");
 
   // Each load reads the wave's 16 rows through a buffer range that ends at
   // the unit's last row (rows past it load as zeros and are discarded), with
@@ -503,16 +541,18 @@ __global__ __launch_bounds__(kThreads) void kpass_quad_kernel(
     }
   };
   constexpr int TRIP = UNR * TPB;
-  static_assert(kKChunk % (2 * TRIP) == 0, "chunk must be whole pairs of trips");
+  static_assert(KC % (2 * TRIP) == 0, "chunk must be whole pairs of trips");
   uint4 ba[UNR][PIECES], bb[UNR][PIECES];
   load_trip(0, ba);
-  for (int it0 = 0; it0 < kKChunk; it0 += 2 * TRIP) {
+  const int lim = min(KC, (un.n - base + 2 * TRIP - 1) / (2 * TRIP) * (2 * TRIP));
+  kpass_fill<KC>(zsh, lim);
+  for (int it0 = 0; it0 < lim; it0 += 2 * TRIP) {
     load_trip(it0 + TRIP, bb);
     process(it0, ba);
-    load_trip(min(it0 + 2 * TRIP, kKChunk - TRIP), ba);
+    load_trip(min(it0 + 2 * TRIP, KC - TRIP), ba);
     process(it0 + TRIP, bb);
   }
-  kpass_epilogue(un, u, base, trow, zsh, ksq, red, zout, kout, cstat, kchunks, status, uflags,
+  kpass_epilogue<KC>(un, u, base, trow, zsh, ksq, red, zout, kout, cstat, kchunks, status, uflags,
                  chunk);
 }
 
@@ -695,7 +735,7 @@ __device__ __forceinline__ void kpass_tile_chunk(
     load(min(w0 + p0 + 2 * 16 * TT, w0 + WT - 16 * TT), pa);
     compute(w0 + p0 + 16 * TT, pb);
   }
-  kpass_epilogue(un, u, base, trow, zsh, ksq, red, zout, kout, cstat, kchunks, status, uflags,
+  kpass_epilogue<kKChunk>(un, u, base, trow, zsh, ksq, red, zout, kout, cstat, kchunks, status, uflags,
                  chunk);
 }
 
@@ -889,7 +929,7 @@ __global__ __launch_bounds__(kThreads, 2) void kpass_tri_kernel(
   auto after = [&]() {
     if (++done % SPC == 0) {
       const int c = done / SPC - 1;
-      kpass_epilogue(un, u, base0 + c * kKChunk, trow, zsh, ksq, red, zout, kout, cstat, kchunks,
+      kpass_epilogue<kKChunk>(un, u, base0 + c * kKChunk, trow, zsh, ksq, red, zout, kout, cstat, kchunks,
                      status, uflags, chunk0 + c);
     }
   };
@@ -918,16 +958,22 @@ static void kpass_dispatch(const Launch& L, const void* k, bool full, dim3 grid,
         ws_ptr<float>(L.wsp, L.ws.kappa), ws_ptr<float2>(L.wsp, L.ws.cstat), L.ws.kchunks,
         inv_scale, ws_ptr<uint32_t>(L.wsp, L.ws.status), ws_ptr<uint32_t>(L.wsp, L.ws.uflags));
   };
-  if (full) {
-    args(kpass_kernel<T, D, true>);
-  } else if constexpr (std::is_same<T, uint16_t>::value) {
-    kpass_quad_kernel<D><<<grid, kThreads, 0, L.stream>>>(
+  auto quad = [&](auto kern) {
+    kern<<<grid, kThreads, 0, L.stream>>>(
         g, (const uint16_t*)k, ws_ptr<double>(L.wsp, L.ws.mu), ws_ptr<double>(L.wsp, L.ws.lam),
         ws_ptr<float>(L.wsp, L.ws.z), ws_ptr<float>(L.wsp, L.ws.kappa),
         ws_ptr<float2>(L.wsp, L.ws.cstat), L.ws.kchunks, inv_scale,
         ws_ptr<uint32_t>(L.wsp, L.ws.status), ws_ptr<uint32_t>(L.wsp, L.ws.uflags));
+  };
+  const bool small = L.ws.kchunk == kKChunkMin;
+  if (full) {
+    args(kpass_kernel<T, D, true, kKChunk>);
+  } else if constexpr (std::is_same<T, uint16_t>::value) {
+    if (small) quad(kpass_quad_kernel<D, kKChunkMin>);
+    else quad(kpass_quad_kernel<D, kKChunk>);
   } else {
-    args(kpass_kernel<T, D, false>);
+    if (small) args(kpass_kernel<T, D, false, kKChunkMin>);
+    else args(kpass_kernel<T, D, false, kKChunk>);
   }
 }
 
@@ -990,8 +1036,8 @@ hipError_t launch_kpass(const Launch& L, const void* k, const void* q) {
 // in the same order, so all of them use bit-identical (m, Z).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kThreads) void softmax_weights_kernel(
-    Geo g, const float2* __restrict__ cstat, int kchunks, const float* __restrict__ zbuf,
-    const float* __restrict__ kbuf, double inv_d, int wchunks, double* __restrict__ scale_out,
+    Geo g, const float2* __restrict__ cstat, int kchunks, int kchunk, const float* __restrict__ zbuf,
+    const float* __restrict__ kbuf, double inv_d, int wchunks, int wchunk, double* __restrict__ scale_out,
     float* __restrict__ wout) {
   int u, chunk;
   if (!grid_unit_chunk<false>(g, wchunks, u, chunk)) return;
@@ -1004,9 +1050,9 @@ __global__ __launch_bounds__(kThreads) void softmax_weights_kernel(
     if (chunk == 0 && tid == 0) scale_out[u] = 1.0;
     return;
   }
-  const int base = chunk * kWChunk;
+  const int base = chunk * wchunk;
   if (base >= un.n) return;
-  const int nch = (un.n + kKChunk - 1) / kKChunk;
+  const int nch = (un.n + kchunk - 1) / kchunk;
   const float2* cs = cstat + (int64_t)u * kchunks;
   float m = -INFINITY;
   for (int c = tid; c < nch; c += kThreads) m = fmaxf(m, cs[c].x);
@@ -1034,7 +1080,7 @@ __global__ __launch_bounds__(kThreads) void softmax_weights_kernel(
   if (chunk == 0 && tid == 0) scale_out[u] = wscale;
   const double wfac = wscale * inv_d;
   const int64_t trow = token_row(g, un);
-  const int end = min(un.n, base + kWChunk);
+  const int end = min(un.n, base + wchunk);
   // Eq. 8 per token: e = exp(z - m) from the fp32 exponential of the rounded
   // difference, corrected to first order by the difference's rounding error
   // (relative error ~1e-7), alpha = e / Z and 1 - alpha = (Z - e) / Z in fp64,
@@ -1049,7 +1095,7 @@ __global__ __launch_bounds__(kThreads) void softmax_weights_kernel(
     return (float)(rho * rho * (double)kap * wfac);
   };
   constexpr int U4 = 4;
-  static_assert(kWChunk % (U4 * kThreads) == 0, "whole unrolled trips per chunk");
+  static_assert(kWChunkMin % (U4 * kThreads) == 0, "whole unrolled trips per chunk");
   for (int t0 = base + tid; t0 < end; t0 += U4 * kThreads) {
     float z[U4], kq[U4];
 #pragma unroll
@@ -1068,8 +1114,9 @@ hipError_t launch_softmax_weights(const Launch& L) {
   const int wchunks = L.ws.wchunks > 0 ? L.ws.wchunks : 1;
   const dim3 grid((unsigned)chunked_grid(L.geo, wchunks));
   softmax_weights_kernel<<<grid, kThreads, 0, L.stream>>>(
-      L.geo, ws_ptr<float2>(L.wsp, L.ws.cstat), L.ws.kchunks, ws_ptr<float>(L.wsp, L.ws.z),
-      ws_ptr<float>(L.wsp, L.ws.kappa), 1.0 / (double)L.geo.D, wchunks,
+      L.geo, ws_ptr<float2>(L.wsp, L.ws.cstat), L.ws.kchunks, L.ws.kchunk,
+      ws_ptr<float>(L.wsp, L.ws.z), ws_ptr<float>(L.wsp, L.ws.kappa), 1.0 / (double)L.geo.D, wchunks,
+      L.ws.wchunk,
       ws_ptr<double>(L.wsp, L.ws.wscale), ws_ptr<float>(L.wsp, L.ws.wgt));
   return hipGetLastError();
 }
