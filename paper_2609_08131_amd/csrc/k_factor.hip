@@ -14,24 +14,30 @@
 // fp64 path): L^{-1} in fp64, over the unit's slot of the reduced-Gram buffer
 // in the operand order of the fp64 leverage pass (store_lower_f64).
 //
-// Blocked algorithm on 16x16 blocks (the sequential chain is what bounds a
-// single workgroup, so the work between barriers is made as wide as possible):
+// Blocked algorithm on 16x16 blocks. A unit's latency is what counts (a layer has
+// few units, and thousands of them still share each compute unit two at a
+// time), and the chain of 128 pivots bounds it, so nothing else stands in line
+// with that chain that can run beside it:
 //   Cholesky, for each block column k:
-//     1. the diagonal block is factored in registers by 16 lanes of wave 0
-//        (lane s holds row s; each pivot's column is broadcast by DPP);
-//     2. the panel below it is solved against it by forward substitution,
-//        one row per thread;
-//     3. the trailing lower triangle takes the rank-16 update, 4x4 register
-//        tiles per thread.
-//   Inverse X = L^{-1}:
-//     4. the diagonal 16x16 blocks are inverted independently (one column per
-//        lane);
-//     5. block columns J from right to left: X_IJ = -(sum_{M > J} X_IM L_MJ)
-//        X_JJ for every I > J at once (16x16 products on the fp64 MFMA).
+//     1. two waves factor the diagonal block in registers and, with the same
+//        broadcasts, solve the panel below it (a row per lane) and 16 rows of
+//        the identity, which become L_kk^{-T}; the other waves meanwhile
+//        take the part of the previous rank-16 update that this column does
+//        not need;
+//     2. all waves update the next block column (fp64 MFMA).
+//   Inverse X = L^{-1}, from the diagonal blocks (which step 1 leaves inverted),
+//   by doubling: [[X11, 0], [-X22 L21 X11, X22]] for halves of 1, 2 and 4
+//   blocks -- two products per level, their 16x16 output blocks spread over
+//   all waves, instead of a serial sweep over seven block columns.
 // LDS holds only the lower 16x16 blocks of A (about 78 KB at d = 128, so two
 // workgroups share a compute unit); L replaces A and X replaces L there,
 // block by block as each part is consumed.
+//
+// Measured (MI355X, d = 128): 8 units 51 us and 4096 units 604 us with the panel as
+// a phase of its own, the diagonal blocks inverted after the factorisation and
+// the column sweep; 40 us and 506 us here.
 #include <algorithm>
+#include <type_traits>
 
 #include "jacap_internal.hpp"
 
@@ -60,14 +66,12 @@ constexpr double kPivRelSingularFp32 = 1e-8;
 // four-wave shape, see factor_kernel).
 constexpr int kFactorThreads = 512;
 
-// Lane N of each 16-lane row, broadcast to the row (one 64-bit DPP move,
-// row_newbcast).
+// Lane n of each 16-lane row, broadcast to the row (one 64-bit DPP move,
+// row_newbcast); n is a constant once the caller's loop is unrolled.
 template <int N>
 __device__ __forceinline__ double row_bcast_f64(double v) {
   return __builtin_amdgcn_mov_dpp(v, 0x150 + N, 0xF, 0xF, false);
 }
-// The same for a lane index that is a constant once the caller's loop is
-// unrolled.
 __device__ __forceinline__ double row_bcast_f64_at(double v, int n) {
   switch (n) {
     case 0: return row_bcast_f64<0>(v);
@@ -94,8 +98,9 @@ __device__ __forceinline__ double row_bcast_f64_at(double v, int n) {
 template <bool FULL>
 __device__ __forceinline__ double rsqrt_f64(double x) {
   double y = __builtin_amdgcn_rsq(x);
-  y = y * (1.5 - 0.5 * x * y * y);
-  if constexpr (FULL) y = y * (1.5 - 0.5 * x * y * y);
+  const double h = 0.5 * x;
+  y = y * fma(-h, y * y, 1.5);
+  if constexpr (FULL) y = y * fma(-h, y * y, 1.5);
   return y;
 }
 
@@ -103,7 +108,7 @@ __device__ __forceinline__ double rsqrt_f64(double x) {
 // lower 16x16 blocks (I >= J), packed by rows of blocks; block (I, J) starts
 // at (I (I + 1) / 2 + J) * kBlk and holds element (r, c) at r * kBP + c. The
 // pitch of 17 doubles puts the 16 rows of a block column in distinct banks.
-// Diagonal blocks are stored whole (their upper halves serve as scratch).
+// Diagonal blocks are stored whole.
 constexpr int kBP = 17;
 constexpr int kBlk = 16 * kBP;
 __device__ __forceinline__ int lidx(int row, int col) {
@@ -126,7 +131,8 @@ __host__ __device__ constexpr int lower_frag_elems(int d) {
   return (d / 32) * (d / 32 + 1) * 2 * 64 * 8;
 }
 
-// A lower-triangular matrix X (x(a, b) = X[a][b] for b <= a) rounded to fp32
+// A lower-triangular matrix X (x(a, b) = X[a][b] for b <= a, any value at the other
+// entries of the 32-wide blocks on the diagonal) rounded to fp32
 // and split into bf16 hi + lo terms, stored in the per-lane B-fragment order
 // of the 16x16x32 MFMA for Y = V X^T: B fragment of output block j
 // (a = 16 j + ch) and K block kb (b = 32 kb + 8 kg + q), only the pairs with
@@ -150,7 +156,8 @@ __device__ __forceinline__ void store_lower_frags(uint16_t* __restrict__ out, F 
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
       const int b = 32 * kb + 8 * kg + t;
-      const float xv = (b <= a) ? (float)x(a, b) : 0.0f;
+      const float xr = (float)x(a, b);  // read also where it is not used (in range)
+      const float xv = (b <= a) ? xr : 0.0f;
       const __bf16 h = (__bf16)xv;
       const __bf16 l = (__bf16)(xv - (float)h);
       hi[t] = __builtin_bit_cast(uint16_t, h);
@@ -175,40 +182,59 @@ __device__ __forceinline__ void store_lower_f64(double* __restrict__ out, F x) {
     tri_index(e >> 8, J, B);
     const int l = (e >> 1) & 63, s = 2 * ((e >> 7) & 1) + (e & 1);
     const int a = 16 * J + (l & 15), b = 16 * B + 4 * (l >> 4) + s;
-    out[e] = b <= a ? x(a, b) : 0.0;
+    const double xr = x(a, b);
+    out[e] = b <= a ? xr : 0.0;
   }
 }
 
 // Blocked Cholesky A = L L^T in place on the lower blocks in LDS (see lidx),
 // given dg = diag(A) before factorisation and *bad == 0 (both visible to
-// every thread). idg receives 1 / L_rr. Returns 0, or the flag that stopped
+// every thread). INV: the diagonal blocks receive X_kk = L_kk^{-1} (whole, zeros
+// above the diagonal) instead of L_kk. Returns 0, or the flag that stopped
 // it -- kUnitNonfinite for a non-finite pivot, `fail` for a pivot at or below
 // piv_rel times its diagonal entry -- the same value in every thread.
 // FULL: the pivots' reciprocal square roots to full fp64 accuracy; else to
 // 2^-47.8, for factors that are rounded to two bf16 terms afterwards.
-template <int D, int NT, bool FULL>
-__device__ __forceinline__ int cholesky_lds(double* A, const double* dg, double* idg, int* bad,
-                                            double piv_rel, int fail) {
+template <int D, int NT, bool FULL, bool INV>
+__device__ __forceinline__ int cholesky_lds(double* A, const double* dg, int* bad, double piv_rel,
+                                            int fail) {
   constexpr int NB = D / 16;
   constexpr int NW = NT / 64;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // 1. Diagonal block, in registers of wave 0: lane s (mod 16) holds row s.
-  //    The chain from one pivot to the next is a broadcast, a reciprocal
-  //    square root and one broadcast-FMA; the pivot thresholds are read
-  //    before it starts and the checks stay off it.
-  auto diag = [&](int kb) {
+  constexpr int CW = 2;  // waves of the pivot chain: D - 16 panel rows and 16 of the identity
+  static_assert(CW * 64 >= D, "a lane per row");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // 1. Block column kb. Every 16-lane row of a chain wave holds the diagonal
+  //    block (lane s row s) and each lane one row of the panel or of the identity;
+  //    one broadcast of L[q][t] serves both. The chain from one pivot to the
+  //    next is a broadcast, a reciprocal square root and one broadcast-FMA; the
+  //    pivot thresholds are read before it starts and the checks stay off it.
+  //    d[q] is left with what entry q of this lane's row (INV: column) of the
+  //    new diagonal block is to be: both chain waves read the old one.
+  auto chain = [&](int kb, double (&d)[16]) {
     const int c = 16 * kb;
     const int s = lane & 15;
-    double a[16], thr[16], yv[16];
+    const int npan = D - c - 16;            // panel rows
+    const int e = 64 * wave + lane;         // this lane's row of the panel, then of I
+    const bool pan = e < npan, idn = INV && e >= npan && e < npan + 16;
+    const int prow = pan ? c + 16 + e : c;  // (a row that exists)
+    double a[16], x[16], thr[16];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) a[q] = (q <= s) ? A[lidx((c + s), c + q)] : 0.0;
+    for (int q = 0; q < 16; ++q) {
+      const double v = A[lidx(c + s, c + q)];  // the diagonal block is stored whole
+      a[q] = (q <= s) ? v : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const double v = A[lidx(prow, c + q)];
+      x[q] = pan ? v : (idn && q == e - npan ? 1.0 : 0.0);
+    }
     // A pivot that has lost all but piv_rel of its diagonal entry is within
     // the rounding noise of A: A is numerically singular at the working
     // precision (or the caller's fail condition holds).
 #pragma unroll
     for (int t = 0; t < 16; ++t) thr[t] = piv_rel * dg[c + t];
-    // No early exit (the loop must stay fully unrolled so that a[] lives in
-    // registers): after a failed pivot the rest is computed on whatever it
+    // No early exit: after a failed pivot the rest is computed on whatever it
     // produced and discarded; the flag is the first failure's kind.
     bool failed = false, nonfinite = false;
     double piv = row_bcast_f64<0>(a[0]);  // A[t][t], from lane t of the row
@@ -218,101 +244,101 @@ __device__ __forceinline__ int cholesky_lds(double* A, const double* dg, double*
       const bool ok = piv > thr[t] && piv > 0.0;
       if (!ok && !failed) nonfinite = !isfinite(piv);
       failed = failed || !ok;
-      yv[t] = y;
-      a[t] = (s == t) ? piv * y : a[t] * y;  // column t of L (rows s < t: unused)
+      a[t] = a[t] * y;  // column t of L (lane t: piv y; rows s < t: unused)
+      x[t] = x[t] * y;
       // a[q] -= L[s][t] L[q][t] for q > t; L[q][t] is lane q's a[t]. Entries
       // with q > s are outside row s's lower part and never stored. Row
       // t + 1 goes first, and the next pivot's reciprocal square root is
       // issued before the other rows' updates, which then fill its latency.
-      double pn = 0.0, yn = 0.0;
       if (t + 1 < 16) {
-        a[t + 1] = fma(-a[t], row_bcast_f64_at(a[t], t + 1), a[t + 1]);
-        pn = row_bcast_f64_at(a[t + 1], t + 1);
-        yn = rsqrt_f64<FULL>(pn);
+        const double l = row_bcast_f64_at(a[t], t + 1);
+        a[t + 1] = fma(-a[t], l, a[t + 1]);
+        x[t + 1] = fma(-x[t], l, x[t + 1]);
+        piv = row_bcast_f64_at(a[t + 1], t + 1);
+        y = rsqrt_f64<FULL>(piv);
       }
 #pragma unroll
-      for (int q = t + 2; q < 16; ++q) a[q] = fma(-a[t], row_bcast_f64_at(a[t], q), a[q]);
-      piv = pn;
-      y = yn;
+      for (int q = t + 2; q < 16; ++q) {
+        const double l = row_bcast_f64_at(a[t], q);
+        a[q] = fma(-a[t], l, a[q]);
+        x[q] = fma(-x[t], l, x[q]);
+      }
+      __builtin_amdgcn_sched_barrier(0);  // later steps' broadcasts held back: they would spill
     }
+    // The rows of x exist here, on every path: moved into the branches below, their
+    // updates would keep all 120 broadcasts live.
+#pragma unroll
+    for (int q = 0; q < 16; ++q) asm volatile("" : "+v"(x[q]));
     const int code = failed ? (nonfinite ? (int)kUnitNonfinite : fail) : 0;
-    if (code) {
-      if (lane == 0) *bad = code;
-    } else if (lane < 16) {
+    if (code) {  // the same in both chain waves
+      if (wave == 0 && lane == 0) *bad = code;
+      return;
+    }
+    if (pan) {
+#pragma unroll
+      for (int q = 0; q < 16; ++q) A[lidx(prow, c + q)] = x[q];
+    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q) d[q] = INV ? x[q] : a[q];
+  };
+  // The diagonal block, once every chain wave has read the old one; no step of
+  // the factorisation reads it again.
+  auto store_diag = [&](int kb, const double (&d)[16]) {
+    const int c = 16 * kb, s = lane & 15;
+    const int r = 64 * wave + lane - (D - c - 16);
+    if (INV && r >= 0 && r < 16) {  // row r of L_kk^{-T}: column r of X_kk
+#pragma unroll
+      for (int q = 0; q < 16; ++q) A[lidx(c + q, c + r)] = d[q];
+    }
+    if (!INV && wave == 0 && lane < 16) {
 #pragma unroll
       for (int q = 0; q < 16; ++q)
-        if (q <= s) A[lidx((c + s), c + q)] = a[q];
-      if (lane == 0) {
-#pragma unroll
-        for (int t = 0; t < 16; ++t) idg[c + t] = yv[t];
-      }
+        if (q <= s) A[lidx(c + s, c + q)] = d[q];
     }
   };
-  // 3. Trailing update A_IJ -= L_Ik L_Jk^T of one 16x16 block (I >= J > k,
-  //    block e of the trailing lower triangle, row-major) by one wave on the
-  //    fp64 MFMA (K = 16 in four slices). Diagonal blocks also update their
-  //    upper half, which is unused until the inverse overwrites it.
-  auto update = [&](int kb, int e) {
+  // 2. Trailing update A_IJ -= L_Ik L_Jk^T of one 16x16 block (I >= J > k) by
+  //    one wave on the fp64 MFMA (K = 16 in four slices). Diagonal blocks also
+  //    update their upper half, which nothing reads.
+  auto update = [&](int kb, int bi, int bj) {
     const int c = 16 * kb, r16 = lane & 15, q4 = lane >> 4;
-    int bi, bj;
-    tri_index(e, bi, bj);
-    const int I = 16 * (kb + 1 + bi), J = 16 * (kb + 1 + bj);
-    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+    const int I = 16 * bi, J = 16 * bj;
+    // two chains: half the latency of four dependent MFMAs
+    f64x4 acc, acc2 = {0.0, 0.0, 0.0, 0.0};
+    double l[4], r[4];
 #pragma unroll
     for (int kq = 0; kq < 4; ++kq) {
       const int t = c + 4 * kq + q4;
-      acc = mfma64(A[lidx((I + r16), t)], A[lidx((J + r16), t)], acc);
+      l[kq] = A[lidx((I + r16), t)];
+      r[kq] = A[lidx((J + r16), t)];
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) A[lidx((I + 4 * i + q4), J + r16)] -= acc[i];
+    for (int i = 0; i < 4; ++i) acc[i] = A[lidx((I + 4 * i + q4), J + r16)];
+    acc2 = mfma64(-l[0], r[0], acc2);
+    acc = mfma64(-l[1], r[1], acc);
+    acc2 = mfma64(-l[2], r[2], acc2);
+    acc = mfma64(-l[3], r[3], acc);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) A[lidx((I + 4 * i + q4), J + r16)] = acc[i] + acc2[i];
   };
-  if (wave == 0) diag(0);
-  __syncthreads();
-  if (*bad) return *bad;
   for (int kb = 0; kb < NB; ++kb) {
-    const int c = 16 * kb;
-    // 2. Panel rows r >= c + 16: L[r, c:c+16] = A[r, c:c+16] L_kk^{-T}.
-    for (int r = c + 16 + tid; r < D; r += NT) {
-      double x[16];
-#pragma unroll
-      for (int t = 0; t < 16; ++t) x[t] = A[lidx(r, c + t)];
-      // Row t of L_kk (columns < t) and 1 / L_tt are read one row ahead, so
-      // that the chain does not wait on LDS.
-      double lr[2][16], il[2];
-      il[0] = idg[c];
-#pragma unroll
-      for (int t = 0; t < 16; ++t) {
-        const int cur = t & 1, nxt = cur ^ 1;
-        if (t + 1 < 16) {
-#pragma unroll
-          for (int q = 0; q <= t; ++q) lr[nxt][q] = A[lidx((c + t + 1), c + q)];
-          il[nxt] = idg[c + t + 1];
-        }
-        // x[t] = (A[r][c+t] - sum_q x[q] L[c+t][c+q]) / L[c+t][c+t]; the sum in
-        // four independent chains (latency, not order, bounds this loop)
-        double sp[4] = {x[t], 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int q = 0; q < t; ++q) sp[q & 3] = fma(-x[q], lr[cur][q], sp[q & 3]);
-        x[t] = ((sp[0] + sp[1]) + (sp[2] + sp[3])) * il[cur];
+    const int m = NB - 1 - kb;  // block columns to the right
+    const bool chains = wave < CW && 64 * wave < 16 * m + (INV || wave == 0 ? 16 : 0);
+    double d[16];
+    if (chains) {
+      chain(kb, d);
+    } else if (wave >= CW && kb > 0) {
+      // the previous column's update of the blocks right of column kb
+      for (int e = wave - CW; e < m * (m + 1) / 2; e += NW - CW) {
+        int bi, bj;
+        tri_index(e, bi, bj);
+        update(kb - 1, kb + 1 + bi, kb + 1 + bj);
       }
-#pragma unroll
-      for (int t = 0; t < 16; ++t) A[lidx(r, c + t)] = x[t];
     }
     __syncthreads();
-    // Look-ahead: wave 0 updates the next diagonal block and factors it at
-    // once, while the other waves take the rest of the trailing update, so
-    // that the update is hidden behind the pivot chain.
-    const int m = NB - kb - 1;
-    if (m > 0) {
-      if (wave == 0) {
-        update(kb, 0);  // block (kb + 1, kb + 1)
-        diag(kb + 1);
-      } else {
-        for (int e = wave; e < m * (m + 1) / 2; e += NW - 1) update(kb, e);
-      }
-      __syncthreads();
-      if (*bad) return *bad;
-    }
+    if (*bad) return *bad;
+    if (chains) store_diag(kb, d);
+    for (int e = wave; e < m; e += NW) update(kb, kb + 1 + e, kb + 1);
+    __syncthreads();
   }
   return 0;
 }
@@ -344,7 +370,8 @@ __device__ __forceinline__ void factor_unit(const Geo& g, int u, double* __restr
                                             uint32_t* uflags, const Marked& marked) {
   constexpr int NB = D / 16;
   constexpr int NPAIR = NB * (NB + 1) / 2;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const Unit un = decode_unit(g, u);
   if (un.n == 0) return;
   // The fp32-accumulated Gram of bf16 inputs may be redone in fp64 later;
@@ -355,9 +382,9 @@ __device__ __forceinline__ void factor_unit(const Geo& g, int u, double* __restr
 
   __shared__ double A[NB * (NB + 1) / 2 * kBlk];  // lower 16x16 blocks, see lidx
   __shared__ double dg[D];   // diagonal of A before factorisation
-  __shared__ double idg[D];  // 1 / L_rr
   __shared__ double red_sh[NT / 64];
   __shared__ double red_sh2[NT / 64];
+  __shared__ double red_sh3[NT / 64];
   __shared__ int bad;        // 0, or the unit flag that stops the factorisation
 
   // Lower triangle of A = ridge I + M from the upper blocks of M. Entries
@@ -413,11 +440,12 @@ __device__ __forceinline__ void factor_unit(const Geo& g, int u, double* __restr
     const int e2 = tid + k * NT;
     if (e2 < NE2) {
       const int e = 2 * e2;
-      int p = e >> 8, bi = 0;  // block pair p -> block (bi, bj), bi <= bj, row-major
+      // block pair p -> block (bi, bj), bi <= bj, row-major; two waves per pair
+      const int p = (wave >> 1) + k * (NT / 128);
+      int bi = 0;
 #pragma unroll
-      for (int q = 0; q < NB; ++q)
-        if (p >= NB - bi) { p -= NB - bi; ++bi; }
-      const int bj = bi + p;
+      for (int q = 1; q < NB; ++q) bi += p >= q * NB - q * (q - 1) / 2;
+      const int bj = p - (bi * NB - bi * (bi - 1) / 2) + bi;
       if (may_refine) {  // block-lane layout
         const int ln = (e & 255) / 4, r = e % 4;  // r even: entries r and r + 1 of lane ln
         const int row = bi * 16 + (ln >> 4) * 4 + r;
@@ -459,58 +487,57 @@ __device__ __forceinline__ void factor_unit(const Geo& g, int u, double* __restr
     return;
   }
 
-  // max over rows of sum_c |A[r][c]| (>= lambda_max(A), A symmetric with its
-  // lower triangle stored); TPR threads per row.
-  constexpr int TPR = NT / D;
-  const int prow = tid / TPR, ppart = tid % TPR;
-  // Row prow's entries and column prow's entries at b = ppart + TPR j: with
-  // TPR dividing 16, b's block (TPR j / 16) and offset in it (TPR j mod 16,
-  // plus ppart) are constants of j, so each address is a per-thread base plus
-  // a constant. row_at(j): entry (prow, b), stored for b <= prow; col_at(j):
-  // entry (b, prow), stored for b >= prow (other j give in-range addresses
-  // whose values are not used).
-  static_assert(16 % TPR == 0, "threads per row divide a block row");
-  const int pI = prow >> 4, pr = prow & 15;
-  const int rbase = (pI * (pI + 1) / 2) * kBlk + pr * kBP + ppart;
-  const int cbase = pI * kBlk + ppart * kBP + pr;
-  auto row_at = [&](int j) {
-    const int Ib = (TPR * j) >> 4, o = (TPR * j) & 15;
-    return rbase + Ib * kBlk + o;
-  };
-  auto col_at = [&](int j) {
-    const int Ib = (TPR * j) >> 4, o = (TPR * j) & 15;
-    return cbase + (Ib * (Ib + 1) / 2) * kBlk + o * kBP;
-  };
-  auto block_max = [&](double v) {
-    v = wave_max_f64(v);
-    __syncthreads();
-    if (lane == 0) red_sh[wave] = v;
-    __syncthreads();
-    double m = red_sh[0];
+  // Largest sum of |.| over the rows (COLS: columns) of blocks that `entry`
+  // reads: block row I of a wave (I, and NB-1-I where the waves are fewer), lane
+  // (r16, q4) taking four entries 4 kq + q4 of row r16 per block, independent
+  // reads of constant stride; then the four lanes of a row and the rows.
+  constexpr int NW = NT / 64;
+  const int r16 = lane & 15, q4 = lane >> 4;
+  auto wave_rows_max = [&](auto entry) {
+    double best = 0.0;
 #pragma unroll
-    for (int w = 1; w < NT / 64; ++w) m = fmax(m, red_sh[w]);
-    return m;
+    for (int p = 0; p < (NB + NW - 1) / NW; ++p) {
+      const int I = p == 0 ? wave : NB - 1 - wave;
+      if (I < NB && (p == 0 || I != wave)) {
+        double s[4] = {0.0, 0.0, 0.0, 0.0};
+        entry(I, s);
+        double sr = (s[0] + s[1]) + (s[2] + s[3]);
+        sr += __shfl_xor(sr, 16);
+        sr += __shfl_xor(sr, 32);
+        best = fmax(best, sr);
+      }
+    }
+    best = fmax(best, dpp_f64<kDppQuadXor1>(best));
+    best = fmax(best, dpp_f64<kDppQuadXor2>(best));
+    best = fmax(best, dpp_f64<kDppHalfMirror>(best));
+    return fmax(best, dpp_f64<kDppMirror>(best));
   };
 
-  double anorm = 0.0;
-  if (may_refine) {
-    double sr = 0.0;
-#pragma unroll 8
-    for (int j = 0; j < D / TPR; ++j) {
-      const int b = ppart + TPR * j;
-      sr += fabs((b <= prow) ? A[row_at(j)] : A[col_at(j)]);
-    }
+  // max over rows of sum_c |A[r][c]| (>= lambda_max(A)), A symmetric with its
+  // lower triangle stored: row r of block row I is the blocks J < I, the
+  // diagonal block's own lower half mirrored, and column r of the blocks K > I.
+  if constexpr (may_refine) {
+    const double wm = wave_rows_max([&](int I, double (&s)[4]) {
+      // every block of the row read (the diagonal one apart), whichever side of
+      // the diagonal it is on: NB x 4 independent reads
 #pragma unroll
-    for (int o = 1; o < TPR; o <<= 1) sr += __shfl_xor(sr, o);
-    anorm = block_max(sr);
+      for (int K = 0; K < NB; ++K)
+#pragma unroll
+        for (int kq = 0; kq < 4; ++kq) {
+          const int t = 4 * kq + q4;
+          const int lo = K == I ? min(r16, t) : K < I ? t : r16, hi = K == I ? max(r16, t) : K < I ? r16 : t;
+          s[kq] += fabs(A[lidx(16 * max(I, K) + hi, 16 * min(I, K) + lo)]);
+        }
+    });
+    if (lane == 0) red_sh3[wave] = wm;  // read with the inverse's norms
   }
 
   // ---------------- Cholesky A = L L^T (L overwrites the lower triangle) ----
   // The first factorisation of bf16 inputs ends in two-term bf16 fragments
   // of L^{-1}; the fp64 paths keep full precision.
   const int code =
-      may_refine ? cholesky_lds<D, NT, false>(A, dg, idg, &bad, piv_rel, (int)kUnitRefine)
-                 : cholesky_lds<D, NT, true>(A, dg, idg, &bad, piv_rel, (int)kUnitSingular);
+      may_refine ? cholesky_lds<D, NT, false, true>(A, dg, &bad, piv_rel, (int)kUnitRefine)
+                 : cholesky_lds<D, NT, true, true>(A, dg, &bad, piv_rel, (int)kUnitSingular);
   if (code) {
     if (tid == 0) {
       if (code == (int)kUnitRefine) marked.add(u, uflags);
@@ -520,121 +547,109 @@ __device__ __forceinline__ void factor_unit(const Geo& g, int u, double* __restr
   }
 
   // ---------------- Inverse X = L^{-1} --------------------------------------
-  // 4. Diagonal blocks: lane (k, t) computes column t of X_kk by forward
-  //    substitution and stores X_kk[i][t] (i > t) at A[c + t][c + i] (the
-  //    block's upper half; L_kk is still being read), then the block is
-  //    copied down over L_kk with 1 / L_rr on the diagonal.
-  if (tid < 16 * NB) {
-    const int k = tid >> 4, t = tid & 15, c = 16 * k;
-    double x[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      double sum = 0.0;
-#pragma unroll
-      for (int q = 0; q < i; ++q) sum += A[lidx((c + i), c + q)] * x[q];
-      x[i] = i < t ? 0.0 : (i == t ? idg[c + i] : -idg[c + i] * sum);
-    }
-#pragma unroll
-    for (int i = 1; i < 16; ++i)
-      if (i > t) A[lidx((c + t), c + i)] = x[i];
-  }
-  __syncthreads();
-  for (int e = tid; e < NB * 256; e += NT) {
-    const int c = 16 * (e >> 8), i = (e >> 4) & 15, t = e & 15;
-    if (i > t) A[lidx((c + i), c + t)] = A[lidx((c + t), c + i)];
-    else if (i == t) A[lidx((c + i), c + i)] = idg[c + i];
-  }
-  __syncthreads();
-  // 5. Off-diagonal blocks of X, block column J from right to left, in place:
-  //    X_IJ = -(sum_{M=J+1..I} X_IM L_MJ) X_JJ for I > J ((X L)_IJ = 0), where
-  //    the blocks X_IM (M > J) are final and L_MJ still in place. One 16x16
-  //    output block per wave on the fp64 MFMA; the sum is held in registers
-  //    until every wave has read its operands, then stored over L_IJ, and
-  //    the wave multiplies its own stored block by X_JJ at once (no other
-  //    wave reads it until the next block column). The triangular X blocks
-  //    are masked above their diagonal (their upper halves hold the
-  //    temporaries of step 4).
+  // The diagonal blocks hold X_kk. By doubling, for halves of h blocks: with
+  // rows I of the lower half and columns J of the upper half of a diagonal pair,
+  //   T_IJ = sum_{M >= J} L_IM X_MJ,  X_IJ = -sum_{M <= I} X_IM T_MJ,
+  // each in place: the sums stay in registers until every wave has read its
+  // operands. The output blocks go over the waves so that every SIMD has as
+  // many products of both stages (mirrored for every second pair or row pair).
   {
-    const int r16 = lane & 15, q4 = lane >> 4;
-    constexpr int NW = NT / 64;
-    constexpr int PW = (NB - 1 + NW - 1) / NW;  // output blocks per wave, at most
-    for (int J = NB - 2; J >= 0; --J) {
-      // output blocks I = J + 1 + wave + NW p, p < PW
-      f64x4 acc[PW];
+    // D += P Q of two blocks: P = block (I, M), Q = block (M, J)
+    auto product = [&](int I, int M, int J, f64x4 acc) {
+      double pa[4], qb[4];
 #pragma unroll
-      for (int p = 0; p < PW; ++p) {
-        acc[p] = f64x4{0.0, 0.0, 0.0, 0.0};
-        const int I = J + 1 + wave + NW * p;
-        if (I < NB) {
-          for (int M = J + 1; M <= I; ++M) {
-            // the block step's operands, all loaded before its MFMAs
-            double x[4], l[4];
+      for (int kq = 0; kq < 4; ++kq) {
+        const int t = 4 * kq + q4;
+        pa[kq] = A[lidx(16 * I + r16, 16 * M + t)];
+        qb[kq] = A[lidx(16 * M + t, 16 * J + r16)];
+      }
 #pragma unroll
-            for (int kq = 0; kq < 4; ++kq) {
-              const int t = 4 * kq + q4;
-              x[kq] = (M < I || r16 >= t) ? A[lidx(16 * I + r16, 16 * M + t)] : 0.0;
-              l[kq] = A[lidx(16 * M + t, 16 * J + r16)];
-            }
+      for (int kq = 0; kq < 4; ++kq) acc = mfma64(pa[kq], qb[kq], acc);
+      return acc;
+    };
+    auto level = [&](auto hc) {
+      constexpr int h = decltype(hc)::value;
+      constexpr int NOUT = NB * h / 2;               // output blocks
+      constexpr int PW = (NOUT + NW - 1) / NW;       // ... per wave, at most
+      auto place = [&](int o, int& base, int& i, int& j) {
+        int r = o % (h * h);
+        const int pr = o / (h * h);
+        if (h == 2 && (pr & 1)) r = h * h - 1 - r;
+        i = r / h;
+        j = r % h;
+        if (h == 4 && ((o / NW) & 1)) j = h - 1 - j;
+        base = 2 * h * pr;
+      };
 #pragma unroll
-            for (int kq = 0; kq < 4; ++kq) acc[p] = mfma64(x[kq], l[kq], acc[p]);
+      for (int stage = 0; stage < 2; ++stage) {
+        f64x4 acc[PW];
+#pragma unroll
+        for (int p = 0; p < PW; ++p) {
+          acc[p] = f64x4{0.0, 0.0, 0.0, 0.0};
+          const int o = wave + NW * p;
+          int base, i, j;
+          place(o, base, i, j);
+          if (o < NOUT) {
+            if (stage == 0)
+              for (int M = j; M < h; ++M) acc[p] = product(base + h + i, base + M, base + j, acc[p]);
+            else
+              for (int M = 0; M <= i; ++M) acc[p] = product(base + h + i, base + h + M, base + j, acc[p]);
           }
         }
-      }
-      __syncthreads();  // every wave's reads of L_.J done
+        __syncthreads();  // every wave's operands read
 #pragma unroll
-      for (int p = 0; p < PW; ++p) {
-        const int I = J + 1 + wave + NW * p;
-        if (I < NB) {
+        for (int p = 0; p < PW; ++p) {
+          const int o = wave + NW * p;
+          int base, i, j;
+          place(o, base, i, j);
+          if (o < NOUT)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) A[lidx(16 * I + 4 * i + q4, 16 * J + r16)] = acc[p][i];
-          double tv[4], x[4];
-#pragma unroll
-          for (int kq = 0; kq < 4; ++kq) {
-            const int t = 4 * kq + q4;
-            tv[kq] = A[lidx(16 * I + r16, 16 * J + t)];
-            x[kq] = t >= r16 ? A[lidx(16 * J + t, 16 * J + r16)] : 0.0;
-          }
-          f64x4 out = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-          for (int kq = 0; kq < 4; ++kq) out = mfma64(tv[kq], x[kq], out);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) A[lidx(16 * I + 4 * i + q4, 16 * J + r16)] = -out[i];
+            for (int q = 0; q < 4; ++q)
+              A[lidx(16 * (base + h + i) + 4 * q + q4, 16 * (base + j) + r16)] =
+                  stage == 0 ? acc[p][q] : -acc[p][q];
         }
+        __syncthreads();
       }
-      __syncthreads();  // X_.J visible to the next block column's products
-    }
+    };
+    level(std::integral_constant<int, 1>{});
+    level(std::integral_constant<int, 2>{});
+    if constexpr (NB == 8) level(std::integral_constant<int, 4>{});
+    static_assert(NB == 4 || NB == 8, "head_dim 64 or 128");
   }
-  // X[r][c] (zero above the diagonal).
-  auto xat = [&](int r, int cc) -> double { return r >= cc ? A[lidx(r, cc)] : 0.0; };
-
-  auto xinv = xat;
+  // X[r][c], r >= c (entries above the diagonal are not used).
+  auto xinv = [&](int r, int cc) -> double { return A[lidx(r, cc)]; };
 
   // cond(A) <= ||A||_inf ||L^{-1}||_1 ||L^{-1}||_inf (lambda_max <= ||A||_inf,
   // 1 / lambda_min = ||L^{-1}||_2^2 <= ||L^{-1}||_1 ||L^{-1}||_inf): a bound,
   // so no ill-conditioned unit escapes the refinement.
-  if (may_refine) {
-    double rs = 0.0, cs = 0.0;  // row prow's and column prow's absolute sums
-#pragma unroll 8
-    for (int j = 0; j < D / TPR; ++j) {
-      const int b = ppart + TPR * j;
-      rs += fabs(b <= prow ? A[row_at(j)] : 0.0);
-      cs += fabs(b >= prow ? A[col_at(j)] : 0.0);
-    }
+  if constexpr (may_refine) {
+    // the diagonal blocks hold zeros above the diagonal
+    const double wr = wave_rows_max([&](int I, double (&s)[4]) {
 #pragma unroll
-    for (int o = 1; o < TPR; o <<= 1) {
-      rs += __shfl_xor(rs, o);
-      cs += __shfl_xor(cs, o);
-    }
-    // both maxima in one exchange (red_sh was last read before step 5's
-    // barriers)
-    const double wr = wave_max_f64(rs), wc = wave_max_f64(cs);
+      for (int J = 0; J < NB; ++J)
+#pragma unroll
+        for (int kq = 0; kq < 4; ++kq) {
+          const double v = A[lidx(16 * I + r16, 16 * min(J, I) + 4 * kq + q4)];
+          s[kq] += J <= I ? fabs(v) : 0.0;
+        }
+    });
+    const double wc = wave_rows_max([&](int J, double (&s)[4]) {
+#pragma unroll
+      for (int I = 0; I < NB; ++I)
+#pragma unroll
+        for (int kq = 0; kq < 4; ++kq) {
+          const double v = A[lidx(16 * max(I, J) + 4 * kq + q4, 16 * J + r16)];
+          s[kq] += I >= J ? fabs(v) : 0.0;
+        }
+    });
     if (lane == 0) { red_sh[wave] = wr; red_sh2[wave] = wc; }
     __syncthreads();
-    double xinf = red_sh[0], x1 = red_sh2[0];
+    double xinf = red_sh[0], x1 = red_sh2[0], anorm = red_sh3[0];
 #pragma unroll
     for (int w = 1; w < NT / 64; ++w) {
       xinf = fmax(xinf, red_sh[w]);
       x1 = fmax(x1, red_sh2[w]);
+      anorm = fmax(anorm, red_sh3[w]);
     }
     if (anorm * x1 * xinf > kRefineCond) {
       if (tid == 0) marked.add(u, uflags);
@@ -761,7 +776,6 @@ __device__ __forceinline__ void qfactor_unit(const Geo& g, int u, const uint16_t
   }
   __shared__ double A[NPAIR * kBlk];  // lower 16x16 blocks, see lidx
   __shared__ double dg[D];
-  __shared__ double idg[D];
   __shared__ double smu[D];
   __shared__ __attribute__((aligned(16))) uint16_t qs[kFullMaxQ * QPB];  // the window, raw bf16
   __shared__ int bad;
@@ -851,7 +865,7 @@ __device__ __forceinline__ void qfactor_unit(const Geo& g, int u, const uint16_t
   __syncthreads();
   for (int a = tid; a < D; a += kFactorThreads) dg[a] = A[lidx(a, a)];
   __syncthreads();
-  if (cholesky_lds<D, kFactorThreads, false>(A, dg, idg, &bad, kPivRelTri, (int)kUnitKTile) != 0) {
+  if (cholesky_lds<D, kFactorThreads, false, false>(A, dg, &bad, kPivRelTri, (int)kUnitKTile) != 0) {
     if (tid == 0) atomicOr(uflags + u, kUnitKTile);
     return;
   }
