@@ -9,9 +9,15 @@
 // shapes (1024 threads with 8192-entry lists, or 256 threads with 1024-entry
 // lists for batches of many units with small effective budgets).
 //
-// Fast path (sample select): keys of a fixed sample of the unit (up to 128
-// blocks of 64 contiguous tokens, evenly spaced; 32 in the narrow shape)
-// bracket T between two sample
+// Everything is counted with wave ballots: a wave takes 64 consecutive positions
+// per step, so popcounts of the lanes below give every position's place, and the
+// waves exchange one word each at one barrier. The key of a given rank among
+// keys held in registers is found two bits at a time (rank_search), without
+// atomics, whose conflicts on the few exponents of the scores cost most.
+//
+// Units that fit a thread's registers are ranked and emitted directly. Longer
+// ones take a sample select: keys of a fixed sample of the unit (blocks of 64
+// contiguous tokens, evenly spaced) bracket T between two sample
 // order statistics lo <= T <= hi. One ordered pass over the scores then
 // collects, in position order, the tokens with key > hi (kept for sure) and
 // the band lo <= key <= hi (candidates) into LDS; T and the emission are
@@ -19,8 +25,14 @@
 // tokens above hi, at least budget at or above lo) and that both lists fit;
 // otherwise the unit takes the general path: a three-pass radix select over
 // the scores (11 + 11 + 10 bits, MSB first) and an ordered emission pass.
-// Both paths give the same, deterministic result.
+// All paths give the same, deterministic result.
+//
+// Measured (MI355X, the phase with its events; histogram ranks and staged chunks
+// everywhere, and now): 256 units of 32768 tokens 40 and 31 us, of 131072 tokens 89
+// and 78 us; 4096 units of 2176 tokens, evicted slots, 176 and 80 us; 1024 units of
+// 16512 tokens keeping 16384 100 and 62 us; 8 units of 8192 tokens 20 and 21 us.
 #include <algorithm>
+#include <type_traits>
 
 #include "jacap_internal.hpp"
 
@@ -34,14 +46,20 @@ namespace jacap {
 template <int THREADS, int CAP>
 struct SelCfg {
   static constexpr int kThreads = THREADS;
-  static constexpr int kPer = 8;                   // tokens per thread per staged chunk
-  static constexpr int kChunk = kPer * THREADS;    // scores per staged chunk
+  static constexpr int kWaves = THREADS / 64;
+  static constexpr int kPer = 8;                   // tokens per thread per chunk of the ordered pass
+  static constexpr int kChunk = kPer * THREADS;    // scores per chunk
   static constexpr int kCand = CAP;                // candidate band capacity
   static constexpr int kSure = CAP;                // kept-for-sure list capacity
-  static constexpr int kSample = kChunk / 64;      // sample: <= kSample blocks of 64 tokens
+  static constexpr int kCandPer = CAP / THREADS;   // candidates per thread
+  static constexpr bool kWide = THREADS == 1024;
+  // Longest unit of the direct path. Its search costs 16 steps of three counts per
+  // key and thread; in the wide shape two keys are where a sample costs less.
+  static constexpr int kDirect = kWide ? 2048 : 4096;
+  static constexpr int kSample = kChunk / 64;      // sample of the staged path: <= kSample blocks
 };
-using SelWide = SelCfg<1024, 8192>;   // 141 KB of LDS: one workgroup per CU
-using SelNarrow = SelCfg<256, 1024>;  // 29 KB: five per CU
+using SelWide = SelCfg<1024, 8192>;   // 140 KB of LDS: one workgroup per CU
+using SelNarrow = SelCfg<256, 1024>;  // 25 KB: six per CU
 // Batches of at least this many units take the narrow shape when no unit
 // ranks more than half its list capacity.
 constexpr int kSelNarrowUnits = 1024;
@@ -55,17 +73,110 @@ __device__ __forceinline__ uint32_t score_key(float f) {
 
 template <class C>
 struct SelShared {
-  // staged chunk keys (one pad word per 8: the per-thread reads of 8
-  // consecutive keys are then bank-conflict free) / sample keys / kept
-  // candidate positions / evicted positions
-  uint32_t stage[C::kChunk + C::kChunk / 8];
   uint32_t ckey[C::kCand];    // candidate keys (position order)
   int32_t cpos[C::kCand];     // candidate positions
   int32_t gpos[C::kSure];     // kept-for-sure positions (position order)
+  // kept candidates (position order) / evicted positions; in the staged path also
+  // the chunk's keys (one pad word per 8: the per-thread reads of 8 consecutive
+  // keys are then bank-conflict free) and the sample's
+  int32_t kept[C::kWide ? C::kCand : C::kChunk + C::kChunk / 8];
   uint32_t hist[2048];
-  uint32_t scan[C::kThreads / 64 + 1];
+  uint32_t scan[C::kWaves + 1];
   uint32_t bc[2];
+  uint2 cnt[2][C::kWaves];    // counts of the waves, one of the two sets per exchange
 };
+
+// Per-wave words a and b (uniform in each wave, every 16-bit field's sum below
+// 65536): their sums over the workgroup's waves, and over the waves before this
+// one. One barrier; `par` alternates the exchange buffer.
+template <class C>
+__device__ __forceinline__ uint2 wave_exchange(uint2 v, SelShared<C>& sh, int& par, uint2& before) {
+  static_assert(C::kWaves <= 16, "one DPP row of wave words");
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (lane == 0) sh.cnt[par][wave] = v;
+  __syncthreads();
+  uint2 w = make_uint2(0u, 0u);
+  if ((lane & 15) < C::kWaves) w = sh.cnt[par][lane & 15];
+  uint2 b = (lane & 15) < wave ? w : make_uint2(0u, 0u);
+  auto row_sum = [](uint32_t x) {
+    auto d = [](uint32_t y, auto c) {
+      return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)y, decltype(c)::value, 0xF, 0xF, true);
+    };
+    x += d(x, std::integral_constant<int, kDppQuadXor1>{});
+    x += d(x, std::integral_constant<int, kDppQuadXor2>{});
+    x += d(x, std::integral_constant<int, kDppHalfMirror>{});
+    x += d(x, std::integral_constant<int, kDppMirror>{});
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+  };
+  before = make_uint2(row_sum(b.x), row_sum(b.y));
+  par ^= 1;
+  return make_uint2(row_sum(w.x), row_sum(w.y));
+}
+
+// A threshold for the rank `rank` (1 = largest) among the keys k[0 .. PER) of every
+// thread (0 in unused places): the largest T with at least `rank` keys >= T,
+// found two bits at a time from the top -- or, as soon as some prefix c has
+// rank .. rank + slack keys >= c, T = c - 1, whose lower bits do not matter. `above`
+// = the number of keys > T: with slack 0 the top `rank` keys are those > T and
+// the first rank - above of those == T.
+template <class C, int PER>
+__device__ __forceinline__ uint32_t rank_search(const uint32_t (&k)[PER], uint32_t rank,
+                                                uint32_t slack, SelShared<C>& sh, int& par,
+                                                uint32_t& above) {
+  static_assert(PER * C::kThreads < 65536, "counts in 16-bit fields");
+  uint32_t T = 0u;
+  above = 0u;
+#pragma unroll 1
+  for (int bit = 30; bit >= 0; bit -= 2) {
+    uint32_t c[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const uint32_t cand = T | (uint32_t)(d + 1) << bit;
+      c[d] = 0;
+#pragma unroll
+      for (int j = 0; j < PER; ++j) c[d] += __popcll(__ballot(k[j] >= cand));
+    }
+    uint2 before;
+    const uint2 s = wave_exchange<C>(make_uint2(c[0] | c[1] << 16, c[2]), sh, par, before);
+    const uint32_t n1 = s.x & 0xFFFFu, n2 = s.x >> 16, n3 = s.y;
+    const uint32_t d = n3 >= rank ? 3u : n2 >= rank ? 2u : n1 >= rank ? 1u : 0u;
+    const uint32_t nd = d == 3 ? n3 : d == 2 ? n2 : n1;  // keys >= the digit's prefix (d > 0)
+    T |= d << bit;
+    if (d > 0 && nd <= rank + slack) {
+      above = nd;
+      return T - 1u;
+    }
+    above = d == 3 ? above : d == 2 ? n3 : d == 1 ? n2 : n1;
+  }
+  return T;
+}
+
+// Places of the kept keys among k[0 .. PER) of every thread, in the order (wave,
+// j, lane): keys > T, and the first `need` of those == T. f(j, place) for each
+// kept key of this thread; `valid(j)` excludes unused places.
+template <class C, int PER, class Valid, class F>
+__device__ __forceinline__ void emit_kept(const uint32_t (&k)[PER], uint32_t T, uint32_t need,
+                                          SelShared<C>& sh, int& par, Valid valid, F f) {
+  const uint64_t below = ((uint64_t)1 << (threadIdx.x & 63)) - 1;
+  uint32_t ng = 0, ne = 0;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    ng += __popcll(__ballot(valid(j) && k[j] > T));
+    ne += __popcll(__ballot(valid(j) && k[j] == T));
+  }
+  uint2 before;
+  wave_exchange<C>(make_uint2(ng, ne), sh, par, before);
+  uint32_t g = before.x, e = before.y;  // keys > T, keys == T so far
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const bool gt = valid(j) && k[j] > T, eq = valid(j) && k[j] == T;
+    const uint64_t bg = __ballot(gt), be = __ballot(eq);
+    const uint32_t gb = g + __popcll(bg & below), eb = e + __popcll(be & below);
+    if (gt || (eq && eb < need)) f(j, gb + min(eb, need));
+    g += __popcll(bg);
+    e += __popcll(be);
+  }
+}
 
 // Exclusive prefix sum over C::kThreads values (one per thread), fixed order:
 // a wave scan, then every thread adds the totals of the waves before its own
@@ -184,12 +295,159 @@ __device__ __forceinline__ int lower_bound_lds(const int32_t* a, int cnt, int32_
   return lo;
 }
 
-// TOP-kk of key_at(0 .. n-1) by (key desc, position asc), written to out[0 ..
-// kk) in ascending position order (0 < kk < n).
+// The candidates' part of the sample select, PER keys per thread (C::kThreads *
+// PER >= ccnt): the kept ones' positions, ascending, into sh.kept[0 .. r).
+template <class C, int PER>
+__device__ __forceinline__ void keep_candidates(uint32_t ccnt, uint32_t r, SelShared<C>& sh,
+                                                int& par) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t k[PER];
+  auto index = [&](int j) { return (uint32_t)((wave * PER + j) * 64 + lane); };
+#pragma unroll
+  for (int j = 0; j < PER; ++j) k[j] = index(j) < ccnt ? sh.ckey[index(j)] : 0u;
+  uint32_t above;
+  const uint32_t T = rank_search<C, PER>(k, r, 0u, sh, par, above);
+  emit_kept<C, PER>(k, T, r - above, sh, par, [&](int j) { return index(j) < ccnt; },
+                    [&](int j, uint32_t place) { sh.kept[place] = sh.cpos[index(j)]; });
+}
+
+// Every key in a register: PER per thread (n <= C::kThreads * PER).
+template <class C, int PER, class RawAt, class Conv>
+__device__ void select_direct(RawAt raw_at, Conv conv, int n, int kk, int32_t* out,
+                              SelShared<C>& sh) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int par = 0;
+  uint32_t k[PER];
+  auto pos = [&](int j) { return (wave * PER + j) * 64 + lane; };
+  float raw[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) raw[j] = raw_at(min(pos(j), n - 1));
+#pragma unroll
+  for (int j = 0; j < PER; ++j) k[j] = pos(j) < n ? conv(raw[j]) : 0u;
+  uint32_t above;
+  const uint32_t T = rank_search<C, PER>(k, (uint32_t)kk, 0u, sh, par, above);
+  emit_kept<C, PER>(k, T, (uint32_t)kk - above, sh, par, [&](int j) { return pos(j) < n; },
+                    [&](int j, uint32_t place) { out[place] = pos(j); });
+}
+
+// Long units, wide shape: sample select, counted with ballots.
 template <class C, class KeyAt, class RawAt, class Conv>
-__device__ void select_unit(KeyAt key_at, RawAt raw_at, Conv conv, int n, int kk, int32_t* out,
+__device__ void select_sampled(KeyAt key_at, RawAt raw_at, Conv conv, int n, int kk, int32_t* out,
+                               SelShared<C>& sh) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int par = 0;
+  // Bracket [lo, hi] of T from a sample of PER keys per thread.
+  uint32_t lo = 0u, hi = 0xFFFFFFFFu;
+  auto bracket = [&](auto perc) {
+    constexpr int PER = decltype(perc)::value;
+    constexpr int NBLK = C::kThreads * PER / 64;   // sampled 64-token blocks, at most
+    const int nb64 = (n + 63) / 64;
+    const int q = (nb64 + NBLK - 1) / NBLK;        // every q-th block
+    const int nsb = (nb64 + q - 1) / q;
+    const int S = (nsb - 1) * 64 + min(64, n - (nsb - 1) * q * 64);
+    uint32_t k[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int blk = wave * PER + j, p = blk * q * 64 + lane;
+      k[j] = blk < nsb && p < n ? key_at(p) : 0u;
+    }
+    const double ks = (double)kk * (double)S / (double)n;
+    const int delta = (int)(4.0 * sqrt(ks)) + 16;
+    const int kr = max(1, (int)(ks + 0.5));
+    const int r_lo = min(S, kr + delta);
+    uint32_t dummy;
+    lo = rank_search<C, PER>(k, (uint32_t)r_lo, (uint32_t)r_lo / 8, sh, par, dummy);
+    // An upper bound only where all above lo may not fit the candidates' list
+    // (and the band does not reach the top of the sample).
+    if (kr - delta >= 1 && (int64_t)r_lo * n > (int64_t)S * (C::kCand / 2))
+      hi = rank_search<C, PER>(k, (uint32_t)(kr - delta), 0u, sh, par, dummy);
+  };
+  if (n <= 16384) bracket(std::integral_constant<int, 1>{});
+  else bracket(std::integral_constant<int, 2>{});
+
+  // One ordered pass: kept-for-sure (key > hi) and candidates (lo <= key <= hi),
+  // a chunk's scores loaded one chunk ahead (kept raw until used, so that no
+  // conversion waits on the loads early).
+  const uint64_t below = ((uint64_t)1 << lane) - 1;
+  float nxt[C::kPer];
+  auto pos = [&](int base, int j) { return base + (wave * C::kPer + j) * 64 + lane; };
+  auto load_chunk = [&](int base) {
+#pragma unroll
+    for (int j = 0; j < C::kPer; ++j) nxt[j] = raw_at(min(pos(base, j), n - 1));
+  };
+  load_chunk(0);
+  uint32_t gcnt = 0, ccnt = 0;
+  for (int base = 0; base < n; base += C::kChunk) {
+    uint32_t k[C::kPer];
+#pragma unroll
+    for (int j = 0; j < C::kPer; ++j) k[j] = conv(nxt[j]);
+    if (base + C::kChunk < n) load_chunk(base + C::kChunk);  // uniform
+    uint64_t bg[C::kPer], bcd[C::kPer];
+    uint32_t ng = 0, nc = 0;
+#pragma unroll
+    for (int j = 0; j < C::kPer; ++j) {
+      const bool valid = pos(base, j) < n;
+      bg[j] = __ballot(valid && k[j] > hi);
+      bcd[j] = __ballot(valid && k[j] >= lo && k[j] <= hi);
+      ng += __popcll(bg[j]);
+      nc += __popcll(bcd[j]);
+    }
+    uint2 before;
+    const uint2 tot = wave_exchange<C>(make_uint2(ng, nc), sh, par, before);
+    uint32_t go = gcnt + before.x, co = ccnt + before.y;
+#pragma unroll
+    for (int j = 0; j < C::kPer; ++j) {
+      if (bg[j] >> lane & 1) {
+        const uint32_t at = go + __popcll(bg[j] & below);
+        if (at < (uint32_t)C::kSure) sh.gpos[at] = pos(base, j);
+      } else if (bcd[j] >> lane & 1) {
+        const uint32_t at = co + __popcll(bcd[j] & below);
+        if (at < (uint32_t)C::kCand) { sh.ckey[at] = k[j]; sh.cpos[at] = pos(base, j); }
+      }
+      go += __popcll(bg[j]);
+      co += __popcll(bcd[j]);
+    }
+    gcnt += tot.x;
+    ccnt += tot.y;
+  }
+  __syncthreads();
+  const bool ok = gcnt < (uint32_t)kk && gcnt + ccnt >= (uint32_t)kk &&
+                  gcnt <= (uint32_t)C::kSure && ccnt <= (uint32_t)C::kCand;
+  if (!ok) {  // uniform: every thread holds the same counts
+    select_general<C>(key_at, n, kk, out, sh);
+    return;
+  }
+
+  // T among the candidates: rank r = kk - gcnt; fewer keys per thread cost less.
+  const uint32_t r = (uint32_t)kk - gcnt;
+  if (ccnt <= (uint32_t)C::kThreads) keep_candidates<C, 1>(ccnt, r, sh, par);
+  else if (ccnt <= 2u * C::kThreads) keep_candidates<C, 2>(ccnt, r, sh, par);
+  else if (ccnt <= 4u * C::kThreads) keep_candidates<C, 4>(ccnt, r, sh, par);
+  else keep_candidates<C, 8>(ccnt, r, sh, par);
+  static_assert(C::kCandPer <= 8, "candidates per thread");
+  __syncthreads();
+  // Merge the two position-ordered lists into out[0 .. kk).
+  for (int a = tid; a < (int)gcnt; a += C::kThreads) {
+    const int32_t p = sh.gpos[a];
+    out[a + lower_bound_lds(sh.kept, (int)r, p)] = p;
+  }
+  for (int b = tid; b < (int)r; b += C::kThreads) {
+    const int32_t p = sh.kept[b];
+    out[b + lower_bound_lds(sh.gpos, (int)gcnt, p)] = p;
+  }
+}
+
+// Long units, narrow shape: the same with histogram ranks (radix_rank) and the
+// chunk's keys staged in LDS, 8 consecutive per thread. Several workgroups share
+// a compute unit here and its one scalar unit, which the ballots of
+// select_sampled keep busy: 4096 units of 4096 to 32768 tokens 178 us, 326 us
+// with ballots.
+template <class C, class KeyAt, class RawAt, class Conv>
+__device__ void select_staged(KeyAt key_at, RawAt raw_at, Conv conv, int n, int kk, int32_t* out,
                             SelShared<C>& sh) {
   static_assert(C::kCand <= C::kChunk + C::kChunk / 8, "kept candidates are merged from stage");
+  uint32_t* stage = reinterpret_cast<uint32_t*>(sh.kept);
   static_assert(C::kSample * 64 <= C::kChunk, "the sample is staged in stage");
   const int tid = threadIdx.x;
   // Bracket [lo, hi] of T from the sample (the whole unit if it fits the band).
@@ -201,7 +459,7 @@ __device__ void select_unit(KeyAt key_at, RawAt raw_at, Conv conv, int n, int kk
     const int last_start = (nsb - 1) * q * 64;
     const int S = (nsb - 1) * 64 + min(64, n - last_start);   // valid samples form a prefix
     for (int j = tid; j < S; j += C::kThreads)
-      sh.stage[j] = key_at((j >> 6) * q * 64 + (j & 63));
+      stage[j] = key_at((j >> 6) * q * 64 + (j & 63));
     __syncthreads();
     const double ks = (double)kk * (double)S / (double)n;
     const int delta = (int)(4.0 * sqrt(ks)) + 16;
@@ -211,8 +469,8 @@ __device__ void select_unit(KeyAt key_at, RawAt raw_at, Conv conv, int n, int kk
     // When the band reaches the top of the sample there is no upper bound:
     // tokens above the sample maximum are candidates too.
     if (kr - delta >= 1)
-      hi = radix_rank<C>([&](int i) { return sh.stage[i]; }, S, (uint32_t)(kr - delta), sh, dummy);
-    lo = radix_rank<C>([&](int i) { return sh.stage[i]; }, S, r_lo, sh, dummy);
+      hi = radix_rank<C>([&](int i) { return stage[i]; }, S, (uint32_t)(kr - delta), sh, dummy);
+    lo = radix_rank<C>([&](int i) { return stage[i]; }, S, r_lo, sh, dummy);
   }
 
   // One ordered pass: kept-for-sure (key > hi) and candidates (lo <= key <= hi).
@@ -232,7 +490,7 @@ __device__ void select_unit(KeyAt key_at, RawAt raw_at, Conv conv, int n, int kk
 #pragma unroll
     for (int j = 0; j < C::kPer; ++j) {
       const int p = base + j * C::kThreads + tid;
-      sh.stage[pad(j * C::kThreads + tid)] = p < n ? conv(nxt[j]) : 0u;
+      stage[pad(j * C::kThreads + tid)] = p < n ? conv(nxt[j]) : 0u;
     }
     if (base + C::kChunk < n) load_chunk(base + C::kChunk);  // uniform
     __syncthreads();
@@ -241,7 +499,7 @@ __device__ void select_unit(KeyAt key_at, RawAt raw_at, Conv conv, int n, int kk
 #pragma unroll
     for (int qd = 0; qd < C::kPer; ++qd) {
       const int p = base + C::kPer * tid + qd;
-      k8[qd] = sh.stage[pad(C::kPer * tid + qd)];
+      k8[qd] = stage[pad(C::kPer * tid + qd)];
       const bool valid = p < n;
       ng += valid && k8[qd] > hi;
       nc += valid && k8[qd] >= lo && k8[qd] <= hi;
@@ -295,11 +553,11 @@ __device__ void select_unit(KeyAt key_at, RawAt raw_at, Conv conv, int n, int kk
     bool keep = false;
     if (key > T) keep = true;
     else if (key == T) { keep = (uint32_t)e < need; ++e; }
-    if (keep) sh.stage[sel_before++] = (uint32_t)sh.cpos[i];
+    if (keep) stage[sel_before++] = (uint32_t)sh.cpos[i];
   }
   __syncthreads();
   // Merge the two position-ordered lists into out[0 .. kk).
-  const int32_t* kept_c = reinterpret_cast<const int32_t*>(sh.stage);
+  const int32_t* kept_c = reinterpret_cast<const int32_t*>(stage);
   for (int a = tid; a < (int)gcnt; a += C::kThreads) {
     const int32_t p = sh.gpos[a];
     out[a + lower_bound_lds(kept_c, (int)r, p)] = p;
@@ -310,65 +568,134 @@ __device__ void select_unit(KeyAt key_at, RawAt raw_at, Conv conv, int n, int kk
   }
 }
 
+// TOP-kk of key_at(0 .. n-1) by (key desc, position asc), written to out[0 ..
+// kk) in ascending position order (0 < kk < n). raw_at / conv: a score as loaded,
+// and its key (loads kept apart from conversions).
+template <class C, class KeyAt, class RawAt, class Conv>
+__device__ __forceinline__ void select_unit(KeyAt key_at, RawAt raw_at, Conv conv, int n, int kk,
+                                            int32_t* out, SelShared<C>& sh) {
+  if (n <= C::kDirect / 2)
+    select_direct<C, C::kDirect / 2 / C::kThreads>(raw_at, conv, n, kk, out, sh);
+  else if (n <= C::kDirect)
+    select_direct<C, C::kDirect / C::kThreads>(raw_at, conv, n, kk, out, sh);
+  else if constexpr (C::kWide)
+    select_sampled<C>(key_at, raw_at, conv, n, kk, out, sh);
+  else
+    select_staged<C>(key_at, raw_at, conv, n, kk, out, sh);
+}
+
+// The complement is ranked instead of the kept tokens when it is the smaller
+// part of the n ranked positions and fits the lists.
+template <class C>
+__device__ __forceinline__ bool ranks_evicted(int n, int kk) {
+  return kk > 0 && kk < n && n - kk < kk && n - kk <= C::kCand;
+}
+
+// slots != null: the evicted-slot lists are wanted (capacity cap per unit); a unit
+// whose evicted tokens are the ranked part writes its list here, and no kept
+// positions, the others leave theirs in idx for evicted_kernel.
 template <class C>
 __global__ __launch_bounds__(C::kThreads) void select_kernel(Geo g, const float* __restrict__ scores,
                                                              int32_t* __restrict__ idx, int budget,
-                                                             int protect) {
+                                                             int protect,
+                                                             int32_t* __restrict__ slots, int cap) {
   __shared__ SelShared<C> sh;
   const int u = blockIdx.x, tid = threadIdx.x;
   const Unit un = decode_unit(g, u);
   int32_t* out = idx + (int64_t)u * budget;
   const int kk_all = min(budget, un.n);
   const float* s = scores + token_row(g, un);
-
-  for (int j = kk_all + tid; j < budget; j += C::kThreads) out[j] = -1;
-  if (kk_all == 0) return;
   // Protected tail: the last p positions are kept; the ranking fills the
   // remaining kk slots from positions 0 .. n-1 (n = n_b - p), whose indices
   // all precede the tail, so the tail simply follows them in idx.
   const int npro = min(protect, kk_all);
   const int n = un.n - npro, kk = kk_all - npro;
+
+  // Keeping more than half: select the n - kk tokens to evict instead (the
+  // last n - kk of the order (key desc, position asc) are the first n - kk of
+  // (~key desc, reversed position asc)), then emit every other position.
+  const bool evicts = ranks_evicted<C>(n, kk);
+  const int m = n - kk;
+  if (evicts) {
+    // evicted, as reversed positions ascending (the candidates' keys are no
+    // longer read when they are written)
+    int32_t* rev = reinterpret_cast<int32_t*>(sh.ckey);
+    select_unit<C>([&](int i) { return ~score_key(s[n - 1 - i]); }, [&](int i) { return s[n - 1 - i]; },
+                [](float f) { return ~score_key(f); }, n, m, rev, sh);
+    __syncthreads();
+    auto evicted = [&](int j) { return n - 1 - rev[m - 1 - j]; };  // ascending
+    if (slots) {
+      int32_t* so = slots + (int64_t)u * cap;
+      for (int j = tid; j < cap; j += C::kThreads) so[j] = j < m ? evicted(j) : -1;
+      return;
+    }
+    for (int j = kk_all + tid; j < budget; j += C::kThreads) out[j] = -1;
+    for (int j = tid; j < npro; j += C::kThreads) out[kk + j] = n + j;
+    if (n <= 2048 * 32) {
+      // a bitmap of the evicted; each wave walks a run of 64-position blocks with
+      // a running count
+      const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+      const int nb64 = (n + 63) / 64, run = (nb64 + C::kWaves - 1) / C::kWaves;
+      for (int j = tid; j < 2 * nb64; j += C::kThreads) sh.hist[j] = 0u;
+      __syncthreads();
+      for (int j = tid; j < m; j += C::kThreads) {
+        const int p = evicted(j);
+        atomicOr(&sh.hist[p >> 5], 1u << (p & 31));
+        sh.kept[j] = p;
+      }
+      __syncthreads();
+      const int b0 = min(nb64, wave * run), b1 = min(nb64, b0 + run);
+      int gone = lower_bound_lds(sh.kept, m, b0 * 64);  // evicted before the block
+      const uint64_t below = ((uint64_t)1 << lane) - 1;
+      for (int b = b0; b < b1; ++b) {
+        const uint64_t ev = (uint64_t)sh.hist[2 * b] | (uint64_t)sh.hist[2 * b + 1] << 32;
+        const int p = 64 * b + lane;
+        if (p < n && !(ev >> lane & 1)) out[p - gone - __popcll(ev & below)] = p;
+        gone += __popcll(ev);
+      }
+      return;
+    }
+    for (int j = tid; j < m; j += C::kThreads) sh.kept[j] = evicted(j);
+    __syncthreads();
+    for (int i = tid; i < n; i += C::kThreads) {
+      const int c = lower_bound_lds(sh.kept, m, i);
+      if (c == m || sh.kept[c] != i) out[i - c] = i;
+    }
+    return;
+  }
+  for (int j = kk_all + tid; j < budget; j += C::kThreads) out[j] = -1;
   for (int j = tid; j < npro; j += C::kThreads) out[kk + j] = n + j;
   if (kk == 0) return;
   if (kk == n) {
     for (int j = tid; j < n; j += C::kThreads) out[j] = j;
     return;
   }
-
-  // Keeping more than half: select the n - kk tokens to evict instead (the
-  // last n - kk of the order (key desc, position asc) are the first n - kk of
-  // (~key desc, reversed position asc)), then emit every other position.
-  const int m = n - kk;
-  if (m < kk && m <= C::kChunk) {
-    select_unit<C>([&](int i) { return ~score_key(s[n - 1 - i]); }, [&](int i) { return s[n - 1 - i]; },
-                [](float f) { return ~score_key(f); }, n, m, out, sh);
-    __syncthreads();  // out[0 .. m): evicted, as reversed positions ascending
-    uint32_t* ev = sh.stage;
-    for (int j = tid; j < m; j += C::kThreads) ev[j] = (uint32_t)(n - 1 - out[m - 1 - j]);
-    __syncthreads();
-    const int32_t* evs = reinterpret_cast<const int32_t*>(ev);
-    for (int i = tid; i < n; i += C::kThreads) {
-      const int c = lower_bound_lds(evs, m, i);
-      if (c == m || evs[c] != i) out[i - c] = i;
-    }
-    return;
-  }
   select_unit<C>([&](int i) { return score_key(s[i]); }, [&](int i) { return s[i]; },
               [](float f) { return score_key(f); }, n, kk, out, sh);
 }
 
-hipError_t launch_select(const Launch& L, const float* scores, int32_t* idx) {
-  const Geo& g = L.geo;
+// The narrow shape: many units, each ranking at most half of its lists (the
+// largest number of tokens any unit ranks is min(B, n - B) at the longest n).
+static bool select_narrow(const Launch& L) {
   const int budget = L.cfg->budget_k;
-  // The largest number of tokens any unit ranks: min(B, n - B) at the longest n.
-  const int kmax = std::min(budget, std::max(0, g.maxn - budget));
-  if (g.U >= kSelNarrowUnits && kmax <= SelNarrow::kCand / 2)
-    select_kernel<SelNarrow><<<g.U, SelNarrow::kThreads, 0, L.stream>>>(g, scores, idx, budget,
-                                                                        L.cfg->protect_last);
-  else
-    select_kernel<SelWide><<<g.U, SelWide::kThreads, 0, L.stream>>>(g, scores, idx, budget,
-                                                                    L.cfg->protect_last);
+  const int kmax = std::min(budget, std::max(0, L.geo.maxn - budget));
+  return L.geo.U >= kSelNarrowUnits && kmax <= SelNarrow::kCand / 2;
+}
+
+static hipError_t select_launch(const Launch& L, const float* scores, int32_t* idx, int32_t* slots,
+                                int cap) {
+  const Geo& g = L.geo;
+  auto go = [&](auto kern, int threads) {
+    kern<<<g.U, threads, 0, L.stream>>>(g, scores, idx, L.cfg->budget_k, L.cfg->protect_last, slots,
+                                        cap);
+  };
+  if (select_narrow(L)) go(select_kernel<SelNarrow>, SelNarrow::kThreads);
+  else go(select_kernel<SelWide>, SelWide::kThreads);
   return hipGetLastError();
+}
+
+hipError_t launch_select(const Launch& L, const float* scores, int32_t* idx) {
+  return select_launch(L, scores, idx, nullptr, 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -381,16 +708,20 @@ hipError_t launch_select(const Launch& L, const float* scores, int32_t* idx) {
 // places the positions p0 + tid, p0 + tid + kThreads, ... (consecutive
 // threads write consecutive slots between kept positions). The tile also
 // writes the -1 padding of the slots [p0, p0 + kEvTile) at or past n - kept,
-// and the last tile every padding slot beyond.
+// and the last tile every padding slot beyond. Units whose list select_kernel has
+// written already are skipped.
 // ---------------------------------------------------------------------------
 constexpr int kEvTile = 4096;
 
+template <class C>
 __global__ __launch_bounds__(kThreads) void evicted_kernel(Geo g, const int32_t* __restrict__ kept,
-                                                           int budget, int32_t* __restrict__ slots,
-                                                           int cap) {
+                                                           int budget, int protect,
+                                                           int32_t* __restrict__ slots, int cap) {
   const int u = blockIdx.y, tile = blockIdx.x, tid = threadIdx.x;
   const Unit un = decode_unit(g, u);
   const int n = un.n, kk = min(budget, n), ne = n - kk;
+  const int npro = min(protect, kk);
+  if (ranks_evicted<C>(n - npro, kk - npro)) return;
   const int32_t* kp = kept + (int64_t)u * budget;
   int32_t* out = slots + (int64_t)u * cap;
   const int p0 = tile * kEvTile;
@@ -416,11 +747,16 @@ hipError_t launch_select_evicted(const Launch& L, const float* scores, int32_t* 
   const int budget = L.cfg->budget_k;
   int32_t* kept = ws_ptr<int32_t>(L.wsp, L.ws.kept);
   if (budget > 0) {
-    const hipError_t e = launch_select(L, scores, kept);
+    const hipError_t e = select_launch(L, scores, kept, slots, cap);
     if (e != hipSuccess) return e;
   }
   const int tiles = std::max(1, (L.geo.maxn + kEvTile - 1) / kEvTile);
-  evicted_kernel<<<dim3(tiles, L.geo.U), kThreads, 0, L.stream>>>(L.geo, kept, budget, slots, cap);
+  auto go = [&](auto kern) {
+    kern<<<dim3(tiles, L.geo.U), kThreads, 0, L.stream>>>(L.geo, kept, budget, L.cfg->protect_last,
+                                                          slots, cap);
+  };
+  if (select_narrow(L)) go(evicted_kernel<SelNarrow>);
+  else go(evicted_kernel<SelWide>);
   return hipGetLastError();
 }
 
