@@ -105,8 +105,12 @@ Workspace layout(const jacap_config* c, const jacap_batch* b, bool greedy = fals
   // Equal sequences whose larger chunks make one nearly full round of the chip
   // take those: no partly filled last round, fewer partials to sum (256 units
   // of 32768 tokens: 3 chunks, 768 workgroups, 385 us and no reduce kernel,
-  // against 8 chunks, 2.7 rounds, 409 + 17 us).
-  if (w.mfma && maxn > 0 && LHT == U * maxn) {
+  // against 8 chunks, 2.7 rounds, 409 + 17 us). Not below ridge 1, where units
+  // just short of the fp64 path would carry the longer fp32 sums into their
+  // scores (256 units of 8192 tokens at ridge 0: 2-norm error 4.9e-7 to 7.2e-7; at
+  // ridge 1 no difference to be seen).
+  if (w.mfma && maxn > 0 && LHT == U * maxn && c->ridge_mode == JACAP_RIDGE_SCALAR &&
+      c->ridge >= 1.0f) {
     const int64_t nch = kGramSlots / U;
     if (nch < w.gchunks && nch * U >= kGramSlots * 9 / 10 &&
         nch >= (maxn + kGChunkMfmaMax - 1) / kGChunkMfmaMax) {
