@@ -152,6 +152,16 @@ constexpr int kComputeUnits = 256;  // MI355X
 // unit, which is what their LDS allows.
 constexpr int kRefineBlocks = 2 * kComputeUnits;
 
+// First partial of a unit in the fp64 Gram over every unit (chunks of `tok`
+// tokens): u * pchunks, or, for sequences of unequal lengths, prow per (layer,
+// head) row and in it t0 / tok + b for sequence b -- at least ceil(n / tok) below
+// the next sequence's, whatever the lengths, with no table of them.
+__device__ __forceinline__ int64_t fp64_slot(const Geo& g, const Unit& un, int u, int pchunks,
+                                             int tok, int prow) {
+  if (prow == 0) return (int64_t)u * pchunks;
+  return (((int64_t)un.l * g.H + un.h) * g.V + un.s) * prow + un.t0 / tok + un.b;
+}
+
 // How the fp64 Gram cuts the R marked units: every unit into `nch` chunks of
 // `tok` tokens (whole kGChunkPrecise), the more of them the fewer units share
 // the buffer's `slots` partials, at most kRefineChunks (the factorisation sums
@@ -199,7 +209,8 @@ struct Workspace {
   size_t gent;     // GreedyEntry [U][ceil(maxn / 256)]  greedy: best of each 256-position block
   size_t total;
   int kchunks, kchunk, wchunks, wchunk, gchunks, gchunk, gparts, lchunks, lchunk;
-  int pchunks, pchunk;  // chunks of the fp64 Gram pass over every unit (fp32 inputs)
+  int pchunks, pchunk;  // chunks of the fp64 Gram pass over every unit (fp32 inputs): at most
+  int prow;             // partials of one (layer, head) row of unequal sequences (0: equal, U x pchunks)
   int pslots;           // fp64 partials the Gram buffer holds
   int plchunks, plchunk;  // chunks of the fp64 leverage pass over every unit
   bool mfma;       // bf16 path (MFMA Gram and leverage)

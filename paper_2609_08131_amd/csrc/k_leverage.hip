@@ -186,7 +186,7 @@ __global__ __launch_bounds__(kThreads, 2) void leverage_f64_kernel(
   constexpr int TT = 2;                        // 16-token tiles per wave
   constexpr int TRIP = TT * 16 * (kThreads / 64);  // tokens per workgroup trip
   constexpr int WORDS = 4 * sizeof(T) / 4;     // 32-bit words of four channels
-  // fp32 tiles are read where they are used: a second set of them would spill
+  // fp32 tiles are read after the previous trip: a second set of them would spill
   constexpr bool AHEAD = sizeof(T) == 2;
   static_assert(TRIP == kLChunkPreciseMin, "the smallest chunk is one trip");
   __shared__ __attribute__((aligned(16))) double X[NPAIR * 256];
@@ -235,18 +235,18 @@ __global__ __launch_bounds__(kThreads, 2) void leverage_f64_kernel(
     };
     const int t_first = base + wave * TT * 16;
     Tiles nxt;
-    if constexpr (AHEAD) load(t_first, nxt);
+    load(t_first, nxt);
     __syncthreads();  // the previous item's X is no longer read
     {
       const double2* src = reinterpret_cast<const double2*>(xred + (int64_t)u * (NPAIR * 256));
       double2* dst = reinterpret_cast<double2*>(X);
+#pragma unroll 6
       for (int e = tid; e < NPAIR * 128; e += kThreads) dst[e] = src[e];
     }
     __syncthreads();
     for (int t0 = t_first; t0 < end; t0 += TRIP) {
       double x[TT][NB][4];
       float w[TT];
-      if constexpr (!AHEAD) load(t0, nxt);
 #pragma unroll
       for (int tt = 0; tt < TT; ++tt) {
         w[tt] = nxt.w[tt];
@@ -288,6 +288,7 @@ __global__ __launch_bounds__(kThreads, 2) void leverage_f64_kernel(
         const int t = t0 + 16 * tt + r16;
         if (q4 == 0 && t < end) scores[trow + t] = (float)((double)w[tt] * ss[tt]);
       }
+      if constexpr (!AHEAD) load(t0 + TRIP, nxt);
     }
   }
 }
