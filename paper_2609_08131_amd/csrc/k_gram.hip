@@ -335,7 +335,10 @@ __global__ __launch_bounds__(kThreads, 2) void gram_mfma_kernel(
 // Measured (MI355X): 241 marked units of 8192 tokens, d = 128, bf16: 3.50 ms as
 // 16x16 register tiles on the fp64 VALU with both operands read from LDS,
 // 0.65 ms here (0.54 ms at the measured fp64 matrix rate of 72 TFLOP/s); 14
-// marked units of 2176 tokens among 4096: 986 us and 25 us.
+// marked units of 2176 tokens among 4096: 986 us and 25 us. Held to 128 VGPRs
+// (fp32 rows one step per turn) two workgroups share a compute unit and one's
+// loads run under the other's products: 8 fp32 sequences of 0 to 8193 tokens,
+// 8 heads, 66 us with one, 57 us with two.
 //
 // Partial: block pair p (row-major over I <= J), entry i of lane l at
 // p * 256 + 64 i + l = M[NB (4 i + l / 16) + I][NB (l % 16) + J].

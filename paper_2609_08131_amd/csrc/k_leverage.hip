@@ -173,7 +173,7 @@ __global__ __launch_bounds__(kThreads, 2) void leverage_mfma_kernel(
 // Measured (MI355X): 241 marked units of 8192 tokens, d = 128, bf16: 8.85 ms
 // with eight threads per token on the fp64 VALU, both operands from LDS,
 // 0.63 ms here (0.54 ms at the measured fp64 matrix rate of 72 TFLOP/s);
-// 14 marked units of 2176 tokens among 4096: 2036 us and 23 us.
+// 14 marked units of 2176 tokens among 4096: 2036 us and 19 us.
 // ---------------------------------------------------------------------------
 template <typename T, int D, bool MARKED>
 __global__ __launch_bounds__(kThreads, 2) void leverage_f64_kernel(
