@@ -139,20 +139,6 @@ Workspace layout(const jacap_config* c, const jacap_batch* b, bool greedy = fals
     w.pchunk = (int)per;
     w.pchunks = maxn > 0 ? (int)((maxn + per - 1) / per) : 0;
     w.pslots = (int)std::min<int64_t>(U * w.pchunks, INT32_MAX);
-    // Unequal sequences of fp32 keys: the partials go by their tokens, not by
-    // the longest one's chunks, so the same number of them cuts the long ones
-    // finer (8 sequences of 0 to 8193 tokens, 8 heads: chunks of 2080 tokens 72 us,
-    // of 448 tokens 57 us and 8 us more in the reduce kernel).
-    const int64_t rows = (int64_t)c->num_layers * c->num_kv_heads * V;
-    if (!w.mfma && LHT != U * maxn) {
-      const int64_t room = w.pslots / rows - b->num_seqs - 1;  // whole chunks of a row
-      const int64_t tok = room > 0 ? std::max<int64_t>(kGChunkPrecise, (b->total_tokens / room + 64) / 64 * 64) : 0;
-      if (tok > 0 && tok < w.pchunk) {
-        w.pchunk = (int)tok;
-        w.pchunks = (int)((maxn + tok - 1) / tok);
-        w.prow = (int)(b->total_tokens / tok + b->num_seqs + 1);
-      }
-    }
   }
   // fp64 leverage chunks of fp32 inputs: kLChunkPrecise tokens, halved (down to
   // kLChunkPreciseMin) while the halved chunks still run in one round, two per

@@ -152,16 +152,6 @@ constexpr int kComputeUnits = 256;  // MI355X
 // unit, which is what their LDS allows.
 constexpr int kRefineBlocks = 2 * kComputeUnits;
 
-// First partial of a unit in the fp64 Gram over every unit (chunks of `tok`
-// tokens): u * pchunks, or, for sequences of unequal lengths, prow per (layer,
-// head) row and in it t0 / tok + b for sequence b -- at least ceil(n / tok) below
-// the next sequence's, whatever the lengths, with no table of them.
-__device__ __forceinline__ int64_t fp64_slot(const Geo& g, const Unit& un, int u, int pchunks,
-                                             int tok, int prow) {
-  if (prow == 0) return (int64_t)u * pchunks;
-  return (((int64_t)un.l * g.H + un.h) * g.V + un.s) * prow + un.t0 / tok + un.b;
-}
-
 // How the fp64 Gram cuts the R marked units: every unit into `nch` chunks of
 // `tok` tokens (whole kGChunkPrecise), the more of them the fewer units share
 // the buffer's `slots` partials, at most kRefineChunks (the factorisation sums
@@ -199,7 +189,8 @@ struct Workspace {
   size_t hscore;   // float  [L][H][G][T]    per-query-head scores (per-head GQA mode)
   size_t kept;     // int32  [B][L][H][budget] kept positions, staged by jacap_select_evicted
   size_t gram;     // per-chunk partial Grams: [U][gchunks][NPAIR*256] fp32 (bf16 MFMA pass)
-                   // or fp64 partials, pslots of NPAIR*256 (fp64 pass); one buffer for both
+                   // or fp64 partials, pslots of NPAIR*256 (fp64 pass: [U][pchunks], or the
+                   // marked units' by list entry, see RefineCut); one buffer for both
   size_t gram_red; // double [U][NPAIR*256]  the reduced Gram (gram_reduced), in its partials'
                    // layout; after an fp64 factorisation, L^{-1} in fp64 MFMA operand
                    // order (see k_factor.hip)
@@ -209,8 +200,7 @@ struct Workspace {
   size_t gent;     // GreedyEntry [U][ceil(maxn / 256)]  greedy: best of each 256-position block
   size_t total;
   int kchunks, kchunk, wchunks, wchunk, gchunks, gchunk, gparts, lchunks, lchunk;
-  int pchunks, pchunk;  // chunks of the fp64 Gram pass over every unit (fp32 inputs): at most
-  int prow;             // partials of one (layer, head) row of unequal sequences (0: equal, U x pchunks)
+  int pchunks, pchunk;  // chunks of the fp64 Gram pass over every unit (fp32 inputs)
   int pslots;           // fp64 partials the Gram buffer holds
   int plchunks, plchunk;  // chunks of the fp64 leverage pass over every unit
   bool mfma;       // bf16 path (MFMA Gram and leverage)

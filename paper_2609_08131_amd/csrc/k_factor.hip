@@ -673,7 +673,7 @@ __device__ __forceinline__ void factor_unit(const Geo& g, int u, double* __restr
 template <int D, bool FRAGS, int NT, int PASS>
 __global__ __launch_bounds__(NT, 512 / NT) void factor_kernel(
     Geo g, double* __restrict__ red, const double* __restrict__ part, int pchunks, int pchunk,
-    int prow, int pslots, const float* __restrict__ part32, int gchunks, int gchunk, int reduced,
+    int pslots, const float* __restrict__ part32, int gchunks, int gchunk, int reduced,
     double ridge, const double* __restrict__ wscale, uint16_t* __restrict__ lfrag,
     uint32_t* status, uint32_t* uflags, Marked marked) {
   constexpr int64_t SZ = (D / 16) * (D / 16 + 1) / 2 * 256;
@@ -684,7 +684,7 @@ __global__ __launch_bounds__(NT, 512 / NT) void factor_kernel(
   };
   if constexpr (PASS == 0) {
     const int u = blockIdx.x;
-    unit(u, part + fp64_slot(g, decode_unit(g, u), u, pchunks, pchunk, prow) * SZ, pchunk);
+    unit(u, part + (int64_t)u * pchunks * SZ, pchunk);
   } else {
     const int nu = (int)*marked.count;
     const RefineCut rc = refine_cut(nu, g.maxn, pslots);
@@ -712,7 +712,7 @@ hipError_t launch_factor(const Launch& L, bool refine) {
   const int blocks = refine ? std::min(g.U, kComputeUnits) : g.U;
   const bool pairs = !refine && g.U > kComputeUnits;  // two workgroups per compute unit
   auto go = [&](auto kern, int nt) {
-    kern<<<blocks, nt, 0, L.stream>>>(g, red, part, L.ws.pchunks, L.ws.pchunk, L.ws.prow, L.ws.pslots, part32,
+    kern<<<blocks, nt, 0, L.stream>>>(g, red, part, L.ws.pchunks, L.ws.pchunk, L.ws.pslots, part32,
                                       L.ws.gchunks, L.ws.gchunk, gram_reduced(L) ? 1 : 0, ridge,
                                       wsc, lf, st, uf, marked);
   };

@@ -338,7 +338,7 @@ __global__ __launch_bounds__(kThreads, 2) void gram_mfma_kernel(
 // marked units of 2176 tokens among 4096: 986 us and 25 us. Held to 128 VGPRs
 // (fp32 rows one step per turn) two workgroups share a compute unit and one's
 // loads run under the other's products: 8 fp32 sequences of 0 to 8193 tokens,
-// 8 heads, 66 us with one, 57 us with two.
+// 8 heads, 72 us with one, 62 us with two.
 //
 // Partial: block pair p (row-major over I <= J), entry i of lane l at
 // p * 256 + 64 i + l = M[NB (4 i + l / 16) + I][NB (l % 16) + J].
@@ -438,7 +438,7 @@ template <typename T, int D, bool MARKED>
 __global__ __launch_bounds__(kF64Threads, 4) void gram_f64_kernel(
     Geo g, const T* __restrict__ v, const float* __restrict__ wbuf,
     const uint32_t* __restrict__ rcount, const int32_t* __restrict__ rlist,
-    double* __restrict__ partials, int pchunks, int pchunk, int prow, int pslots) {
+    double* __restrict__ partials, int pchunks, int pchunk, int pslots) {
   constexpr int NB = D / 16;
   constexpr int NPAIR = NB * (NB + 1) / 2;
   constexpr int NCP = NB / 2;
@@ -466,8 +466,7 @@ __global__ __launch_bounds__(kF64Threads, 4) void gram_f64_kernel(
     const int end = min(un.n, base + tok);
     const T* vb = v + un.l * g.vsl + un.h * g.vsh + un.t0 * g.vst;
     const float* wrow = wbuf + token_row(g, un);
-    const int64_t slot = MARKED ? pair : fp64_slot(g, un, u, pchunks, pchunk, prow) + chunk;
-    double* out = partials + slot * (NPAIR * 256);
+    double* out = partials + pair * (NPAIR * 256);  // every unit: [U][pchunks]; marked ones: RefineCut
     if constexpr (NCP == 4) {
       switch (cp) {
         case 0: gram_f64_item<T, D, 0>(vb, g.vst, wrow, base, end, out, red); break;
@@ -510,7 +509,7 @@ hipError_t launch_gram(const Launch& L, const void* v, bool refine) {
   auto go = [&](auto kern, auto vv) {
     kern<<<blocks, kF64Threads, 0, L.stream>>>(
         g, vv, wb, ws_ptr<uint32_t>(L.wsp, L.ws.status) + 1, ws_ptr<int32_t>(L.wsp, L.ws.rlist),
-        ws_ptr<double>(L.wsp, L.ws.gram), L.ws.pchunks, L.ws.pchunk, L.ws.prow, L.ws.pslots);
+        ws_ptr<double>(L.wsp, L.ws.gram), L.ws.pchunks, L.ws.pchunk, L.ws.pslots);
   };
   if (L.ws.mfma) {
     if (g.D == 128) go(gram_f64_kernel<uint16_t, 128, true>, (const uint16_t*)v);
@@ -528,15 +527,14 @@ hipError_t launch_gram(const Launch& L, const void* v, bool refine) {
 // ---------------------------------------------------------------------------
 template <typename P, int D>
 __global__ __launch_bounds__(kThreads) void gram_reduce_kernel(Geo g, const P* __restrict__ partials,
-                                                               int gchunks, int gchunk, int prow,
+                                                               int gchunks, int gchunk,
                                                                double* __restrict__ red) {
   constexpr int NB = D / 16;
   constexpr int NPAIR = NB * (NB + 1) / 2;
   const int u = blockIdx.x, p = blockIdx.y;
   const Unit un = decode_unit(g, u);
   const int nch = (un.n + gchunk - 1) / gchunk;
-  const P* src = partials + fp64_slot(g, un, u, gchunks, gchunk, prow) * (NPAIR * 256) + p * 256 +
-                 threadIdx.x;
+  const P* src = partials + (int64_t)u * gchunks * (NPAIR * 256) + p * 256 + threadIdx.x;
   double s = 0.0;
 #pragma unroll 8
   for (int c = 0; c < nch; ++c) s += (double)src[(int64_t)c * (NPAIR * 256)];
@@ -553,12 +551,12 @@ hipError_t launch_gram_reduce(const Launch& L) {
   double* red = ws_ptr<double>(L.wsp, L.ws.gram_red);
   if (L.ws.mfma) {
     const float* part = ws_ptr<float>(L.wsp, L.ws.gram);
-    if (g.D == 128) gram_reduce_kernel<float, 128><<<grid, kThreads, 0, L.stream>>>(g, part, L.ws.gchunks, L.ws.gchunk, 0, red);
-    else gram_reduce_kernel<float, 64><<<grid, kThreads, 0, L.stream>>>(g, part, L.ws.gchunks, L.ws.gchunk, 0, red);
+    if (g.D == 128) gram_reduce_kernel<float, 128><<<grid, kThreads, 0, L.stream>>>(g, part, L.ws.gchunks, L.ws.gchunk, red);
+    else gram_reduce_kernel<float, 64><<<grid, kThreads, 0, L.stream>>>(g, part, L.ws.gchunks, L.ws.gchunk, red);
   } else {  // fp64 partials
     const double* part = ws_ptr<double>(L.wsp, L.ws.gram);
-    if (g.D == 128) gram_reduce_kernel<double, 128><<<grid, kThreads, 0, L.stream>>>(g, part, L.ws.pchunks, L.ws.pchunk, L.ws.prow, red);
-    else gram_reduce_kernel<double, 64><<<grid, kThreads, 0, L.stream>>>(g, part, L.ws.pchunks, L.ws.pchunk, L.ws.prow, red);
+    if (g.D == 128) gram_reduce_kernel<double, 128><<<grid, kThreads, 0, L.stream>>>(g, part, L.ws.pchunks, L.ws.pchunk, red);
+    else gram_reduce_kernel<double, 64><<<grid, kThreads, 0, L.stream>>>(g, part, L.ws.pchunks, L.ws.pchunk, red);
   }
   return hipGetLastError();
 }

@@ -101,6 +101,8 @@ static void run_valid(const Shape& s, const char* name) {
     const bool per_head = s.gqa == JACAP_GQA_PER_HEAD && s.Hq > s.H;
     EXPECT(stub::calls[stub::kHeadMean] == (per_head ? 1 : 0));
     EXPECT(stub::last.ws_total <= ws);
+    // every unit of fp32 inputs has fp64 Gram partials of its own, wherever it lies
+    EXPECT(bf || (int64_t)stub::last.units * stub::last.pchunks <= stub::last.pslots);
   } else {
     EXPECT(stub::calls[stub::kInit] == 1 && stub::calls[stub::kGram] == 0);
   }
@@ -260,6 +262,7 @@ int main() {
       {32, 8, 32, 128, 32, 256, 16, {4096, 32768, 5000, 17, 0, 1, 255, 256, 257, 1000, 8193, 20000, 31000, 4097, 9999, 12345},
        JACAP_DTYPE_BF16, JACAP_COV_DIAG, JACAP_GQA_POOLED, JACAP_RIDGE_SCALAR, 0, 1.0f},
       {2, 2, 8, 64, 4, 100, 3, {0, 900, 4000}, JACAP_DTYPE_FP32, JACAP_COV_FULL, JACAP_GQA_PER_HEAD, JACAP_RIDGE_SCALAR, 7, 0.0f},
+      {1, 8, 16, 128, 16, 256, 8, {0, 1, 17, 255, 256, 257, 1000, 8193}, JACAP_DTYPE_FP32, JACAP_COV_DIAG, JACAP_GQA_POOLED, JACAP_RIDGE_SCALAR, 64, 1.0f},
       {4, 8, 32, 128, 64, 1024, 1, {131072}, JACAP_DTYPE_BF16, JACAP_COV_FULL, JACAP_GQA_PER_HEAD, JACAP_RIDGE_SCALAR, 64, 0.5f},
       {1, 2, 4, 128, 8, 32, 2, {300, 77}, JACAP_DTYPE_BF16, JACAP_COV_DIAG, JACAP_GQA_POOLED, JACAP_RIDGE_MATRIX, 0, 0.0f},
       {2, 2, 4, 64, 8, 16, 2, {0, 0}, JACAP_DTYPE_BF16, JACAP_COV_DIAG, JACAP_GQA_POOLED, JACAP_RIDGE_SCALAR, 0, 0.5f},

@@ -11,7 +11,7 @@ enum {
 struct Launch {
   int units, maxn;
   size_t ws_total;
-  int gchunks, pchunks, plchunks;
+  int gchunks, pchunks, pslots, plchunks;
 };
 extern int calls[kNumLaunchers];
 extern Launch last;
