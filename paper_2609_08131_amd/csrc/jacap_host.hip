@@ -92,7 +92,12 @@ Workspace layout(const jacap_config* c, const jacap_batch* b, bool greedy = fals
   // Larger chunks write and re-read fewer partials. The longest sequence is
   // cut into the fewest equal chunks (whole 128-token flush spans) that keep
   // kGramMinBlocks blocks in the grid and no chunk above kGChunkMfmaMax
-  // tokens; chunks stay at least kGChunkMfma tokens.
+  // tokens; chunks stay at least kGChunkMfma tokens. A chunk is also what is
+  // summed in fp32 (the partials are added in fp64), so its size does not depend on
+  // the ridge: 10.9K-token chunks at ridge 1 (256 units of 32768 tokens, one round
+  // of the chip) saved the reduce kernel's 17 us, but the scores' 2-norm error
+  // went from 2.06e-6 to 2.20e-6, and units with large values are no better
+  // conditioned at ridge 1 than others at ridge 0.
   if (w.mfma && maxn > 0) {
     const int64_t span = kGramSpan;
     const int64_t nmin = (kGramMinBlocks + U - 1) / U;
@@ -101,23 +106,6 @@ Workspace layout(const jacap_config* c, const jacap_batch* b, bool greedy = fals
     w.gchunk = (int)std::min<int64_t>(std::max<int64_t>(per, kGChunkMfma), kGChunkMfmaMax);
   }
   w.gchunks = (maxn + w.gchunk - 1) / w.gchunk;
-  const int gchunks_held = w.gchunks;  // the partials that the workspace has room for
-  // Equal sequences whose larger chunks make one nearly full round of the chip
-  // take those: no partly filled last round, fewer partials to sum (256 units
-  // of 32768 tokens: 3 chunks, 768 workgroups, 385 us and no reduce kernel,
-  // against 8 chunks, 2.7 rounds, 409 + 17 us). Not below ridge 1, where units
-  // just short of the fp64 path would carry the longer fp32 sums into their
-  // scores (256 units of 8192 tokens at ridge 0: 2-norm error 4.9e-7 to 7.2e-7; at
-  // ridge 1 no difference to be seen).
-  if (w.mfma && maxn > 0 && LHT == U * maxn && c->ridge_mode == JACAP_RIDGE_SCALAR &&
-      c->ridge >= 1.0f) {
-    const int64_t nch = kGramSlots / U;
-    if (nch < w.gchunks && nch * U >= kGramSlots * 9 / 10 &&
-        nch >= (maxn + kGChunkMfmaMax - 1) / kGChunkMfmaMax) {
-      w.gchunk = (int)(((maxn + nch - 1) / nch + kGramSpan - 1) / kGramSpan * kGramSpan);
-      w.gchunks = (maxn + w.gchunk - 1) / w.gchunk;
-    }
-  }
   w.gparts = 1;
   // Leverage chunks: kLChunkMfma tokens, halved (down to kLChunkMfmaMin) while
   // the grid would have fewer than kLevMinBlocks blocks.
@@ -149,7 +137,7 @@ Workspace layout(const jacap_config* c, const jacap_batch* b, bool greedy = fals
   const int64_t NB = D / 16;
   const int64_t npair = NB * (NB + 1) / 2;
   const int64_t nlp = (NB / 2) * (NB / 2 + 1);
-  const int64_t mfma_part_bytes = w.mfma ? U * (int64_t)gchunks_held * npair * 256 * 4 : 0;
+  const int64_t mfma_part_bytes = w.mfma ? U * (int64_t)w.gchunks * npair * 256 * 4 : 0;
   const int64_t fp64_part_bytes = (int64_t)w.pslots * npair * 256 * 8;
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t r = o; o = align256(o + bytes); return r; };

@@ -24,7 +24,6 @@ constexpr int kTriChunks = 4;         // K-pass chunks per workgroup on that pat
 constexpr int kGChunkMfma = 512;     // tokens per workgroup in the MFMA Gram pass: at least
 constexpr int kGChunkMfmaMax = 16384; // ... and at most (larger chunks: fewer partial Grams)
 constexpr int kGramMinBlocks = 2048;  // chunks are as large as this many blocks in the grid allow
-constexpr int kGramSlots = 3 * 256;   // Gram workgroups that run at once: three per compute unit
 constexpr int kGramSpan = 128;       // tokens between two flushes of the Gram's short fp32 chains
 constexpr int kGChunkPrecise = 128;  // tokens per chunk of the fp64 Gram pass: at least
 constexpr int kPrecisePartials = 256;  // fp64 Gram partials per batch the chunking aims at

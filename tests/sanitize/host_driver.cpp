@@ -253,6 +253,29 @@ static void run_status() {
   EXPECT(strcmp(jacap_status_string(JACAP_ERR_WORKSPACE), "JACAP_ERR_WORKSPACE") == 0);
 }
 
+// The tokens whose products one fp32 partial Gram sums follow from the sizes
+// alone: the same chunks at every ridge.
+static void run_gram_chunks() {
+  for (int d : {64, 128})
+    for (int layers : {32, 24, 12, 4})
+      for (int64_t n : {8192, 32768, 131072}) {
+        int first = -1;
+        for (float ridge : {0.0f, 0.5f, 1.0f, 16.0f}) {
+          Shape s = {layers, 8, 32, d, 32, 512, 1, {n}, JACAP_DTYPE_BF16, JACAP_COV_DIAG,
+                     JACAP_GQA_POOLED, JACAP_RIDGE_SCALAR, 0, ridge};
+          jacap_config c;
+          jacap_batch b;
+          int32_t offs[17];
+          size_t ws = 0;
+          fill(s, &c, &b, offs);
+          EXPECT(jacap_workspace_size(&c, &b, &ws) == JACAP_OK);
+          EXPECT(jacap_score(&c, &b, fake(1), fake(2), fake(3), (float*)fake(4), fake(1000), ws, nullptr) == JACAP_OK);
+          if (first < 0) first = stub::last.gchunks;
+          EXPECT(stub::last.gchunks == first);
+        }
+      }
+}
+
 int main() {
   const Shape shapes[] = {
       // tiny fp32; one Llama layer; long128k; ragged lengths; per-head; FULL; W_O; token-free
@@ -274,6 +297,7 @@ int main() {
     snprintf(name, sizeof(name), "shape %d", i++);
     run_valid(s, name);
   }
+  run_gram_chunks();
   run_invalid();
   run_status();
   if (failures) {
