@@ -924,8 +924,11 @@ hipError_t launch_greedy(const Launch& L, const void* v, int32_t* idx, int32_t* 
   if (bytes <= kGLdsMax) {
     static_assert(kGLdsMax / greedy_lds_bytes(128) <= 64, "a wave holds one block entry per lane");
     auto lds = [&](auto kern, auto vp) {
+      // The limit is state of the function that every host thread shares, so it is the same
+      // for every batch: between another thread's setting and its launch, a
+      // shorter batch's own need would be too small for it.
       const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGLdsMax);
       if (e != hipSuccess) return e;
       kern<<<g.U, kGLdsThreads, bytes, L.stream>>>(g, vp, wb, ridge, wsc, budget, protect, gc, ent, nblk_max,
                                          idx, order, logdet);

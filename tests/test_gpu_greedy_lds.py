@@ -2,9 +2,13 @@
 that end, pick counts around the 64 held in registers, more refreshes per pick
 than it remembers (small ridge), protected tails, and the lengths at which units
 stop fitting in LDS; each path replayed through the fp64 oracle (the checks and
-tolerances of test_gpu_greedy.py)."""
+tolerances of test_gpu_greedy.py); calls of different lengths from several host
+threads at once."""
+
+import threading
 
 import pytest
+import torch
 
 from jacap_synth import make_case
 
@@ -27,3 +31,35 @@ def test_greedy_lds_edges(jacap, n, budget, ridge, dtype, d, protect):  # noqa: 
                      head_dim=d, window=8, dtype=dtype).to("cuda")
     check_greedy(jacap, case, budget, ridge=ridge, protect_last=protect,
                  label=f"lds n={n} ridge={ridge:g}")
+
+
+def test_lengths_from_several_threads(jacap):  # noqa: F811
+    problems = []
+    for n, budget in ((300, 24), (11000, 24)):
+        case = make_case("ragged16", seq_lens=[n], num_layers=1, num_kv_heads=2, num_q_heads=4,
+                         head_dim=64, window=8, dtype="bf16").to("cuda")
+        prob = jacap.prepare_greedy(case.q_win, case.k, case.v, case.seq_offsets, case.seq_lens,
+                                    jacap.Params(budget_k=budget))
+        jacap.run_greedy(prob, case.q_win, case.k, case.v)
+        torch.cuda.synchronize()
+        problems.append((case, prob, torch.cuda.Stream(), prob.order.clone()))
+        prob.order.fill_(-7)
+    errors = []
+
+    def work(case, prob, stream):
+        try:
+            for _ in range(20):
+                jacap.run_greedy(prob, case.q_win, case.k, case.v, stream)
+        except Exception as e:   # noqa: BLE001 (reported by the main thread)
+            errors.append(e)
+
+    torch.cuda.synchronize()
+    threads = [threading.Thread(target=work, args=(c, p, s)) for c, p, s, _ in problems]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not errors
+    for _, prob, _, want in problems:
+        assert torch.equal(prob.order, want)
