@@ -9,33 +9,41 @@
 // shapes (1024 threads with 8192-entry lists, or 256 threads with 1024-entry
 // lists for batches of many units with small effective budgets).
 //
-// Everything is counted with wave ballots: a wave takes 64 consecutive positions
-// per step, so popcounts of the lanes below give every position's place, and the
-// waves exchange one word each at one barrier. The key of a given rank among
-// keys held in registers is found two bits at a time (rank_search), without
-// atomics, whose conflicts on the few exponents of the scores cost most.
+// Three paths (sel_wide_path has the wide shape's rule):
+// * direct: units whose keys fit a thread's registers are ranked and emitted
+//   from there;
+// * sampled (wide shape): a lower bound lo <= T from a small sample, one ordered
+//   pass that collects the candidates, key >= lo, in position order into LDS,
+//   their ranking and emission -- as long as the candidates a sample leaves are few;
+// * staged: a larger sample brackets lo <= T <= hi, so that large budgets too leave
+//   few candidates: the pass collects the tokens with key > hi (kept for sure) and
+//   those of the band. At 8192 sample keys a band of 2 (4 sqrt(ks) + 16) of them (ks =
+//   budget x 8192 / n) outgrows the 8192-entry lists from about 12000 kept of 131072
+//   on.
+// The pass checks that the bounds hold (fewer than budget tokens above hi, at
+// least budget at or above lo) and that the lists fit; otherwise the unit takes
+// the general path: a three-pass radix select over the scores (11 + 11 + 10
+// bits, MSB first) and an ordered emission pass, several times slower. All paths
+// give the same, deterministic result.
 //
-// Units that fit a thread's registers are ranked and emitted directly. Longer
-// ones take a sample select: keys of a fixed sample of the unit (blocks of 64
-// contiguous tokens, evenly spaced) bracket T between two sample
-// order statistics lo <= T <= hi. One ordered pass over the scores then
-// collects, in position order, the tokens with key > hi (kept for sure) and
-// the band lo <= key <= hi (candidates) into LDS; T and the emission are
-// finished in LDS. The pass checks that the bracket holds (fewer than budget
-// tokens above hi, at least budget at or above lo) and that both lists fit;
-// otherwise the unit takes the general path: a three-pass radix select over
-// the scores (11 + 11 + 10 bits, MSB first) and an ordered emission pass.
-// All paths give the same, deterministic result.
+// The first two count with wave ballots: a wave takes 64 consecutive positions per
+// step, so popcounts of the lanes below give every position's place, and the waves
+// exchange one word each at one barrier; ranks among keys held in registers are
+// found two bits at a time (rank_search), without the LDS atomics of a histogram
+// (radix_rank), whose conflicts on the few exponents of the scores cost more
+// while the keys per thread are few.
 //
-// Measured (MI355X, the phase with its events; histogram ranks and staged chunks
-// everywhere, and now): 256 units of 32768 tokens 40 and 31 us, of 131072 tokens 89
-// and 78 us; 4096 units of 2176 tokens, evicted slots, 176 and 80 us; 1024 units of
-// 16512 tokens keeping 16384 100 and 62 us; 8 units of 8192 tokens 20 and 21 us.
+// Measured (MI355X, jacap_select calls; histogram ranks and staged chunks
+// everywhere, and now): 8 units of 32768 tokens keeping 512 32.6 and 22.9 us; 256
+// units of 131072 keeping 1024 68.7 and 48.2, keeping 8192 80.3 and 77.1; 64 units
+// of 262144 keeping 4096 118 and 110; 1024 units of 16512 keeping 16384 85 and 50;
+// 4096 units of 2176 tokens, evicted slots, 167 and 65; 8 units of 8192 tokens 16.2
+// and 16.3.
 #include <algorithm>
 #include <type_traits>
 
 #include "jacap_internal.hpp"
-
+#include "select_plan.hpp"
 
 namespace jacap {
 
@@ -54,22 +62,53 @@ struct SelCfg {
   static constexpr int kCandPer = CAP / THREADS;   // candidates per thread
   static constexpr bool kWide = THREADS == 1024;
   // Longest unit of the direct path. Its search costs 16 steps of three counts per
-  // key and thread; in the wide shape two keys are where a sample costs less.
-  static constexpr int kDirect = kWide ? 2048 : 4096;
+  // key and thread; in the wide shape two keys are where a histogram costs less.
+  static constexpr int kDirect = kWide ? kSelWideDirect : 4096;
   static constexpr int kSample = kChunk / 64;      // sample of the staged path: <= kSample blocks
 };
-using SelWide = SelCfg<1024, 8192>;   // 140 KB of LDS: one workgroup per CU
-using SelNarrow = SelCfg<256, 1024>;  // 25 KB: six per CU
+using SelWide = SelCfg<1024, kSelWideCand>;   // 141 KB of LDS: one workgroup per CU
+using SelNarrow = SelCfg<256, 1024>;          // 29 KB: five per CU
 // Batches of at least this many units take the narrow shape when no unit
 // ranks more than half its list capacity.
 constexpr int kSelNarrowUnits = 1024;
 
 __device__ __forceinline__ uint32_t score_key(float f) {
-  if (f != f) return 0u;          // NaN ranks lowest
-  if (f == 0.0f) f = 0.0f;        // -0 == +0
-  const uint32_t b = __float_as_uint(f);
-  return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+  const float g = f + 0.0f;       // -0 == +0
+  const uint32_t b = __float_as_uint(g);
+  const uint32_t k = b ^ ((uint32_t)((int32_t)b >> 31) | 0x80000000u);  // ~b, or b with its top bit set
+  return g == g ? k : 0u;         // NaN ranks lowest
 }
+
+// The n scores that a unit ranks: kForward, or kReverse: in reverse, by their
+// complemented keys (to find the tokens at the end of the order instead), or either
+// of them as the launch finds (kEither: one kernel body for both).
+enum { kForward = 0, kReverse = 1, kEither = 2 };
+template <int DIR>
+struct RankedScores {
+  const float* s;
+  int n;
+  bool reversed;
+  __device__ __forceinline__ uint32_t flip() const {
+    return DIR == kEither ? (reversed ? ~0u : 0u) : DIR == kReverse ? ~0u : 0u;
+  }
+  __device__ __forceinline__ float raw(int i) const {
+    return s[(int)((uint32_t)i ^ flip()) + (n & (int)flip())];  // s[i], or s[n - 1 - i]
+  }
+  __device__ __forceinline__ uint32_t conv(float f) const { return score_key(f) ^ flip(); }
+  __device__ __forceinline__ uint32_t key(int i) const { return conv(raw(i)); }
+};
+// The list of selected positions: a unit's kept ones in global memory, or (of
+// reversed scores) the evicted ones in LDS.
+template <int DIR>
+struct SelOut {
+  int32_t* global;
+  int32_t* lds;
+  bool reversed;
+  __device__ __forceinline__ void put(int place, int32_t pos) const {
+    if (DIR == kReverse || (DIR == kEither && reversed)) lds[place] = pos;
+    else global[place] = pos;
+  }
+};
 
 template <class C>
 struct SelShared {
@@ -79,7 +118,7 @@ struct SelShared {
   // kept candidates (position order) / evicted positions; in the staged path also
   // the chunk's keys (one pad word per 8: the per-thread reads of 8 consecutive
   // keys are then bank-conflict free) and the sample's
-  int32_t kept[C::kWide ? C::kCand : C::kChunk + C::kChunk / 8];
+  int32_t kept[C::kChunk + C::kChunk / 8];
   uint32_t hist[2048];
   uint32_t scan[C::kWaves + 1];
   uint32_t bc[2];
@@ -113,18 +152,50 @@ __device__ __forceinline__ uint2 wave_exchange(uint2 v, SelShared<C>& sh, int& p
   return make_uint2(row_sum(w.x), row_sum(w.y));
 }
 
+// Bitwise and of v.x and or of v.y over the workgroup's threads (the exchange of
+// wave_exchange).
+template <class C>
+__device__ __forceinline__ uint2 block_and_or(uint2 v, SelShared<C>& sh, int& par) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  auto rows = [](uint2 x) {
+    auto d = [](uint32_t y, auto c) {
+      return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)y, decltype(c)::value, 0xF, 0xF, true);
+    };
+    auto step = [&](auto c) { x = make_uint2(x.x & d(x.x, c), x.y | d(x.y, c)); };
+    step(std::integral_constant<int, kDppQuadXor1>{});
+    step(std::integral_constant<int, kDppQuadXor2>{});
+    step(std::integral_constant<int, kDppHalfMirror>{});
+    step(std::integral_constant<int, kDppMirror>{});
+    return x;
+  };
+  auto at = [](uint32_t x, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)x, l); };
+  v = rows(v);
+  const uint2 w = make_uint2(at(v.x, 0) & at(v.x, 16) & at(v.x, 32) & at(v.x, 48),
+                             at(v.y, 0) | at(v.y, 16) | at(v.y, 32) | at(v.y, 48));
+  if (lane == 0) sh.cnt[par][wave] = w;
+  __syncthreads();
+  uint2 r = make_uint2(~0u, 0u);
+  if ((lane & 15) < C::kWaves) r = sh.cnt[par][lane & 15];
+  r = rows(r);
+  par ^= 1;
+  return make_uint2(at(r.x, 0), at(r.y, 0));
+}
+
 // A threshold for the rank `rank` (1 = largest) among the keys k[0 .. PER) of every
 // thread (0 in unused places): the largest T with at least `rank` keys >= T,
 // found two bits at a time from the top -- or, as soon as some prefix c has
 // rank .. rank + slack keys >= c, T = c - 1, whose lower bits do not matter. `above`
 // = the number of keys > T: with slack 0 the top `rank` keys are those > T and
-// the first rank - above of those == T.
+// the first rank - above of those == T. Where many keys share T's prefix after six
+// steps, the bits in which none of them differs are not searched, which ends the
+// search where many scores are equal (8 units of 512 scores of 15 values 13.5 to 7.9 us).
+constexpr int kTieBit = 20;
 template <class C, int PER>
 __device__ __forceinline__ uint32_t rank_search(const uint32_t (&k)[PER], uint32_t rank,
                                                 uint32_t slack, SelShared<C>& sh, int& par,
                                                 uint32_t& above) {
   static_assert(PER * C::kThreads < 65536, "counts in 16-bit fields");
-  uint32_t T = 0u;
+  uint32_t T = 0u, reach = PER * C::kThreads;  // reach: keys >= T (at most)
   above = 0u;
 #pragma unroll 1
   for (int bit = 30; bit >= 0; bit -= 2) {
@@ -147,29 +218,44 @@ __device__ __forceinline__ uint32_t rank_search(const uint32_t (&k)[PER], uint32
       return T - 1u;
     }
     above = d == 3 ? above : d == 2 ? n3 : d == 1 ? n2 : n1;
+    reach = d > 0 ? nd : reach;
+    if (bit == kTieBit && reach - above > PER * C::kThreads / 32) {
+      uint2 ao = make_uint2(~0u, 0u);  // and / or of the keys with T's prefix (one at least)
+#pragma unroll
+      for (int j = 0; j < PER; ++j)
+        if (k[j] >> kTieBit == T >> kTieBit) ao = make_uint2(ao.x & k[j], ao.y | k[j]);
+      ao = block_and_or<C>(ao, sh, par);
+      const uint32_t differ = ao.x ^ ao.y;
+      if (differ == 0u) return ao.x;
+      bit = ((31 - __clz(differ)) & ~1) + 2;  // the next step is two bits below
+      T = ao.x & ~((1u << bit) - 1u);
+    }
   }
   return T;
 }
 
 // Places of the kept keys among k[0 .. PER) of every thread, in the order (wave,
 // j, lane): keys > T, and the first `need` of those == T. f(j, place) for each
-// kept key of this thread; `valid(j)` excludes unused places.
-template <class C, int PER, class Valid, class F>
+// kept key of this thread. (Unused places hold key 0 and come last, so none of them
+// is among the first `need`.)
+template <class C, int PER, class F>
 __device__ __forceinline__ void emit_kept(const uint32_t (&k)[PER], uint32_t T, uint32_t need,
-                                          SelShared<C>& sh, int& par, Valid valid, F f) {
+                                          SelShared<C>& sh, int& par, F f) {
   const uint64_t below = ((uint64_t)1 << (threadIdx.x & 63)) - 1;
   uint32_t ng = 0, ne = 0;
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
-    ng += __popcll(__ballot(valid(j) && k[j] > T));
-    ne += __popcll(__ballot(valid(j) && k[j] == T));
+    ng += __popcll(__ballot(k[j] > T));
+    ne += __popcll(__ballot(k[j] == T));
   }
   uint2 before;
   wave_exchange<C>(make_uint2(ng, ne), sh, par, before);
   uint32_t g = before.x, e = before.y;  // keys > T, keys == T so far
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
-    const bool gt = valid(j) && k[j] > T, eq = valid(j) && k[j] == T;
+    uint32_t kj = k[j];
+    if constexpr (PER > 4) asm volatile("" : "+v"(kj));  // the ballots above again: kept, they would spill
+    const bool gt = kj > T, eq = kj == T;
     const uint64_t bg = __ballot(gt), be = __ballot(eq);
     const uint32_t gb = g + __popcll(bg & below), eb = e + __popcll(be & below);
     if (gt || (eq && eb < need)) f(j, gb + min(eb, need));
@@ -208,8 +294,8 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t* s
 // (1 = largest, rank <= cnt) among key_at(0 .. cnt-1); `need` = how many keys
 // equal to it fall within the top `rank`.
 template <class C, class KeyAt>
-__device__ uint32_t radix_rank(KeyAt key_at, int cnt, uint32_t rank, SelShared<C>& sh,
-                               uint32_t& need) {
+__device__ __forceinline__ uint32_t radix_rank(KeyAt key_at, int cnt, uint32_t rank,
+                                               SelShared<C>& sh, uint32_t& need) {
   const int tid = threadIdx.x;
   uint32_t prefix = 0u, pmask = 0u, remaining = rank;
   const int shifts[3] = {21, 10, 0};
@@ -254,9 +340,11 @@ __device__ uint32_t radix_rank(KeyAt key_at, int cnt, uint32_t rank, SelShared<C
 
 // General path: radix select over the scores, then an ordered emission pass
 // over contiguous per-thread segments.
-template <class C, class KeyAt>
-__device__ void select_general(KeyAt key_at, int n, int kk, int32_t* out, SelShared<C>& sh) {
-  const int tid = threadIdx.x;
+template <class C, int DIR>
+__device__ __forceinline__ void select_general(const RankedScores<DIR>& rs, int kk,
+                                               const SelOut<DIR>& out, SelShared<C>& sh) {
+  const int tid = threadIdx.x, n = rs.n;
+  auto key_at = [&](int i) { return rs.key(i); };
   uint32_t need;
   const uint32_t T = radix_rank<C>(key_at, n, (uint32_t)kk, sh, need);
   const int seg = (n + C::kThreads - 1) / C::kThreads;
@@ -274,11 +362,11 @@ __device__ void select_general(KeyAt key_at, int n, int kk, int32_t* out, SelSha
     const uint32_t key = key_at(i);
     if (key > T) {
       const uint32_t pos = gt_before + min(eq_before, need);
-      if (pos < (uint32_t)kk) out[pos] = i;
+      if (pos < (uint32_t)kk) out.put((int)pos, i);
       ++gt_before;
     } else if (key == T) {
       const uint32_t pos = gt_before + eq_before;
-      if (eq_before < need && pos < (uint32_t)kk) out[pos] = i;
+      if (eq_before < need && pos < (uint32_t)kk) out.put((int)pos, i);
       ++eq_before;
     }
   }
@@ -295,186 +383,155 @@ __device__ __forceinline__ int lower_bound_lds(const int32_t* a, int cnt, int32_
   return lo;
 }
 
-// The candidates' part of the sample select, PER keys per thread (C::kThreads *
-// PER >= ccnt): the kept ones' positions, ascending, into sh.kept[0 .. r).
-template <class C, int PER>
-__device__ __forceinline__ void keep_candidates(uint32_t ccnt, uint32_t r, SelShared<C>& sh,
-                                                int& par) {
+// The top r of the ccnt candidates, PER keys per thread (C::kThreads * PER >= ccnt):
+// their positions, ascending, to out.
+template <class C, int PER, int DIR>
+__device__ __forceinline__ void keep_candidates(uint32_t ccnt, uint32_t r, const SelOut<DIR>& out,
+                                                SelShared<C>& sh, int& par) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t k[PER];
   auto index = [&](int j) { return (uint32_t)((wave * PER + j) * 64 + lane); };
 #pragma unroll
   for (int j = 0; j < PER; ++j) k[j] = index(j) < ccnt ? sh.ckey[index(j)] : 0u;
-  uint32_t above;
+  uint32_t above;  // (the search's barriers come before the list that may replace ckey)
   const uint32_t T = rank_search<C, PER>(k, r, 0u, sh, par, above);
-  emit_kept<C, PER>(k, T, r - above, sh, par, [&](int j) { return index(j) < ccnt; },
-                    [&](int j, uint32_t place) { sh.kept[place] = sh.cpos[index(j)]; });
+  emit_kept<C, PER>(k, T, r - above, sh, par,
+                    [&](int j, uint32_t place) { out.put((int)place, sh.cpos[index(j)]); });
 }
 
 // Every key in a register: PER per thread (n <= C::kThreads * PER).
-template <class C, int PER, class RawAt, class Conv>
-__device__ void select_direct(RawAt raw_at, Conv conv, int n, int kk, int32_t* out,
-                              SelShared<C>& sh) {
+template <class C, int PER, int DIR>
+__device__ __forceinline__ void select_direct(const RankedScores<DIR>& rs, int kk,
+                                              const SelOut<DIR>& out, SelShared<C>& sh) {
+  const int n = rs.n;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int par = 0;
   uint32_t k[PER];
   auto pos = [&](int j) { return (wave * PER + j) * 64 + lane; };
   float raw[PER];
 #pragma unroll
-  for (int j = 0; j < PER; ++j) raw[j] = raw_at(min(pos(j), n - 1));
+  for (int j = 0; j < PER; ++j) raw[j] = rs.raw(min(pos(j), n - 1));
 #pragma unroll
-  for (int j = 0; j < PER; ++j) k[j] = pos(j) < n ? conv(raw[j]) : 0u;
+  for (int j = 0; j < PER; ++j) {
+    k[j] = pos(j) < n ? rs.conv(raw[j]) : 0u;
+    if (PER > 4 && j % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // the keys' masks would spill
+  }
   uint32_t above;
   const uint32_t T = rank_search<C, PER>(k, (uint32_t)kk, 0u, sh, par, above);
-  emit_kept<C, PER>(k, T, (uint32_t)kk - above, sh, par, [&](int j) { return pos(j) < n; },
-                    [&](int j, uint32_t place) { out[place] = pos(j); });
+  emit_kept<C, PER>(k, T, (uint32_t)kk - above, sh, par,
+                    [&](int j, uint32_t place) { out.put((int)place, pos(j)); });
 }
 
-// Long units, wide shape: sample select, counted with ballots.
-template <class C, class KeyAt, class RawAt, class Conv>
-__device__ void select_sampled(KeyAt key_at, RawAt raw_at, Conv conv, int n, int kk, int32_t* out,
-                               SelShared<C>& sh) {
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+// Long units of the wide shape, where a small sample leaves few enough candidates:
+// sample select, counted with ballots. The sample's rank search costs a step of
+// every wave per two bits, so the sample is small, and its segments short, so that
+// they still meet every run of high scores that a larger sample of 64-token blocks
+// would; an upper bound, whose kept-for-sure tokens shorten the candidates' list,
+// costs a second search and a merge, and is left to select_staged.
+template <class C, int DIR>
+__device__ __forceinline__ bool select_sampled(const RankedScores<DIR>& rs, int kk,
+                                               const SelOut<DIR>& out, SelShared<C>& sh) {
+  const int lane = threadIdx.x & 63, n = rs.n;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int par = 0;
-  // Bracket [lo, hi] of T from a sample of PER keys per thread.
-  uint32_t lo = 0u, hi = 0xFFFFFFFFu;
-  auto bracket = [&](auto perc) {
+  // A lower bound of T from a sample of PER keys per thread.
+  uint32_t lo = 0u;
+  const SelBracket b = sel_sampled_bracket(n, kk);
+  auto bound = [&](auto perc) {
     constexpr int PER = decltype(perc)::value;
-    constexpr int NBLK = C::kThreads * PER / 64;   // sampled 64-token blocks, at most
-    const int nb64 = (n + 63) / 64;
-    const int q = (nb64 + NBLK - 1) / NBLK;        // every q-th block
-    const int nsb = (nb64 + q - 1) / q;
-    const int S = (nsb - 1) * 64 + min(64, n - (nsb - 1) * q * 64);
     uint32_t k[PER];
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-      const int blk = wave * PER + j, p = blk * q * 64 + lane;
-      k[j] = blk < nsb && p < n ? key_at(p) : 0u;
+      const int e = (wave * PER + j) * 64 + lane;   // of the sample
+      const int p = e / kSelSeg * b.q * kSelSeg + e % kSelSeg;
+      k[j] = e < b.S ? rs.key(p) : 0u;
     }
-    const double ks = (double)kk * (double)S / (double)n;
-    const int delta = (int)(4.0 * sqrt(ks)) + 16;
-    const int kr = max(1, (int)(ks + 0.5));
-    const int r_lo = min(S, kr + delta);
     uint32_t dummy;
-    lo = rank_search<C, PER>(k, (uint32_t)r_lo, (uint32_t)r_lo / 8, sh, par, dummy);
-    // An upper bound only where all above lo may not fit the candidates' list
-    // (and the band does not reach the top of the sample).
-    if (kr - delta >= 1 && (int64_t)r_lo * n > (int64_t)S * (C::kCand / 2))
-      hi = rank_search<C, PER>(k, (uint32_t)(kr - delta), 0u, sh, par, dummy);
+    lo = rank_search<C, PER>(k, (uint32_t)b.r_lo, (uint32_t)sel_slack(b), sh, par, dummy);
   };
-  if (n <= 16384) bracket(std::integral_constant<int, 1>{});
-  else bracket(std::integral_constant<int, 2>{});
+  if (sel_sample_per(n) == 1) bound(std::integral_constant<int, 1>{});
+  else bound(std::integral_constant<int, 2>{});
 
-  // One ordered pass: kept-for-sure (key > hi) and candidates (lo <= key <= hi),
-  // a chunk's scores loaded one chunk ahead (kept raw until used, so that no
-  // conversion waits on the loads early).
+  // One ordered pass: the candidates, key >= lo; a chunk's scores loaded one chunk
+  // ahead (kept raw until used, so that no conversion waits on the loads early).
   const uint64_t below = ((uint64_t)1 << lane) - 1;
   float nxt[C::kPer];
   auto pos = [&](int base, int j) { return base + (wave * C::kPer + j) * 64 + lane; };
   auto load_chunk = [&](int base) {
 #pragma unroll
-    for (int j = 0; j < C::kPer; ++j) nxt[j] = raw_at(min(pos(base, j), n - 1));
+    for (int j = 0; j < C::kPer; ++j) nxt[j] = rs.raw(min(pos(base, j), n - 1));
   };
   load_chunk(0);
-  uint32_t gcnt = 0, ccnt = 0;
+  uint32_t ccnt = 0;
   for (int base = 0; base < n; base += C::kChunk) {
     uint32_t k[C::kPer];
 #pragma unroll
-    for (int j = 0; j < C::kPer; ++j) k[j] = conv(nxt[j]);
+    for (int j = 0; j < C::kPer; ++j) k[j] = rs.conv(nxt[j]);
     if (base + C::kChunk < n) load_chunk(base + C::kChunk);  // uniform
-    uint64_t bg[C::kPer], bcd[C::kPer];
-    uint32_t ng = 0, nc = 0;
+    uint64_t cand[C::kPer];
+    uint32_t nc = 0;
 #pragma unroll
     for (int j = 0; j < C::kPer; ++j) {
-      const bool valid = pos(base, j) < n;
-      bg[j] = __ballot(valid && k[j] > hi);
-      bcd[j] = __ballot(valid && k[j] >= lo && k[j] <= hi);
-      ng += __popcll(bg[j]);
-      nc += __popcll(bcd[j]);
+      cand[j] = __ballot(pos(base, j) < n && k[j] >= lo);
+      nc += __popcll(cand[j]);
     }
     uint2 before;
-    const uint2 tot = wave_exchange<C>(make_uint2(ng, nc), sh, par, before);
-    uint32_t go = gcnt + before.x, co = ccnt + before.y;
+    const uint2 tot = wave_exchange<C>(make_uint2(nc, 0u), sh, par, before);
+    uint32_t co = ccnt + before.x;
 #pragma unroll
     for (int j = 0; j < C::kPer; ++j) {
-      if (bg[j] >> lane & 1) {
-        const uint32_t at = go + __popcll(bg[j] & below);
-        if (at < (uint32_t)C::kSure) sh.gpos[at] = pos(base, j);
-      } else if (bcd[j] >> lane & 1) {
-        const uint32_t at = co + __popcll(bcd[j] & below);
-        if (at < (uint32_t)C::kCand) { sh.ckey[at] = k[j]; sh.cpos[at] = pos(base, j); }
+      const uint32_t at = co + __popcll(cand[j] & below);
+      if ((cand[j] >> lane & 1) && at < (uint32_t)C::kCand) {
+        sh.ckey[at] = k[j];
+        sh.cpos[at] = pos(base, j);
       }
-      go += __popcll(bg[j]);
-      co += __popcll(bcd[j]);
+      co += __popcll(cand[j]);
     }
-    gcnt += tot.x;
-    ccnt += tot.y;
+    ccnt += tot.x;
   }
   __syncthreads();
-  const bool ok = gcnt < (uint32_t)kk && gcnt + ccnt >= (uint32_t)kk &&
-                  gcnt <= (uint32_t)C::kSure && ccnt <= (uint32_t)C::kCand;
-  if (!ok) {  // uniform: every thread holds the same counts
-    select_general<C>(key_at, n, kk, out, sh);
-    return;
-  }
-
-  // T among the candidates: rank r = kk - gcnt; fewer keys per thread cost less.
-  const uint32_t r = (uint32_t)kk - gcnt;
-  if (ccnt <= (uint32_t)C::kThreads) keep_candidates<C, 1>(ccnt, r, sh, par);
-  else if (ccnt <= 2u * C::kThreads) keep_candidates<C, 2>(ccnt, r, sh, par);
-  else if (ccnt <= 4u * C::kThreads) keep_candidates<C, 4>(ccnt, r, sh, par);
-  else keep_candidates<C, 8>(ccnt, r, sh, par);
+  // uniform: the same count in every thread
+  if (ccnt < (uint32_t)kk || ccnt > (uint32_t)C::kCand) return false;
+  // T among the candidates; fewer keys per thread cost less.
+  if (ccnt <= (uint32_t)C::kThreads) keep_candidates<C, 1>(ccnt, (uint32_t)kk, out, sh, par);
+  else if (ccnt <= 2u * C::kThreads) keep_candidates<C, 2>(ccnt, (uint32_t)kk, out, sh, par);
+  else if (ccnt <= 4u * C::kThreads) keep_candidates<C, 4>(ccnt, (uint32_t)kk, out, sh, par);
+  else keep_candidates<C, 8>(ccnt, (uint32_t)kk, out, sh, par);
   static_assert(C::kCandPer <= 8, "candidates per thread");
-  __syncthreads();
-  // Merge the two position-ordered lists into out[0 .. kk).
-  for (int a = tid; a < (int)gcnt; a += C::kThreads) {
-    const int32_t p = sh.gpos[a];
-    out[a + lower_bound_lds(sh.kept, (int)r, p)] = p;
-  }
-  for (int b = tid; b < (int)r; b += C::kThreads) {
-    const int32_t p = sh.kept[b];
-    out[b + lower_bound_lds(sh.gpos, (int)gcnt, p)] = p;
-  }
+  return true;
 }
 
-// Long units, narrow shape: the same with histogram ranks (radix_rank) and the
-// chunk's keys staged in LDS, 8 consecutive per thread. Several workgroups share
-// a compute unit here and its one scalar unit, which the ballots of
-// select_sampled keep busy: 4096 units of 4096 to 32768 tokens 178 us, 326 us
-// with ballots.
-template <class C, class KeyAt, class RawAt, class Conv>
-__device__ void select_staged(KeyAt key_at, RawAt raw_at, Conv conv, int n, int kk, int32_t* out,
-                            SelShared<C>& sh) {
+// Long units otherwise: the same with a larger sample of 64-token blocks, histogram
+// ranks (radix_rank) and the chunk's keys staged in LDS, 8 consecutive per thread.
+// In the narrow shape several workgroups share a compute unit and its one scalar
+// unit, which the ballots of select_sampled keep busy (4096 units of 4096 to 32768
+// tokens 178 us, 326 us with ballots); in the wide one the larger sample keeps the
+// candidates of large budgets within their list, and histogram ranks cost less
+// than ballots on that many.
+template <class C, int DIR>
+__device__ __forceinline__ bool select_staged(const RankedScores<DIR>& rs, int kk,
+                                              const SelOut<DIR>& out, SelShared<C>& sh) {
   static_assert(C::kCand <= C::kChunk + C::kChunk / 8, "kept candidates are merged from stage");
   uint32_t* stage = reinterpret_cast<uint32_t*>(sh.kept);
   static_assert(C::kSample * 64 <= C::kChunk, "the sample is staged in stage");
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, n = rs.n;
   // Bracket [lo, hi] of T from the sample (the whole unit if it fits the band).
   uint32_t lo = 0u, hi = 0xFFFFFFFFu;
   if (n > C::kCand) {
-    const int nb64 = (n + 63) / 64;
-    const int q = (nb64 + C::kSample - 1) / C::kSample;  // every q-th 64-token block
-    const int nsb = (nb64 + q - 1) / q;
-    const int last_start = (nsb - 1) * q * 64;
-    const int S = (nsb - 1) * 64 + min(64, n - last_start);   // valid samples form a prefix
-    for (int j = tid; j < S; j += C::kThreads)
-      stage[j] = key_at((j >> 6) * q * 64 + (j & 63));
+    const SelBracket b = sel_bracket(n, kk, 64, C::kSample);
+    for (int j = tid; j < b.S; j += C::kThreads)
+      stage[j] = rs.key((j >> 6) * b.q * 64 + (j & 63));
     __syncthreads();
-    const double ks = (double)kk * (double)S / (double)n;
-    const int delta = (int)(4.0 * sqrt(ks)) + 16;
-    const int kr = max(1, (int)(ks + 0.5));
-    const uint32_t r_lo = (uint32_t)min(S, kr + delta);
     uint32_t dummy;
     // When the band reaches the top of the sample there is no upper bound:
     // tokens above the sample maximum are candidates too.
-    if (kr - delta >= 1)
-      hi = radix_rank<C>([&](int i) { return stage[i]; }, S, (uint32_t)(kr - delta), sh, dummy);
-    lo = radix_rank<C>([&](int i) { return stage[i]; }, S, r_lo, sh, dummy);
+    if (b.r_hi >= 1)
+      hi = radix_rank<C>([&](int i) { return stage[i]; }, b.S, (uint32_t)b.r_hi, sh, dummy);
+    lo = radix_rank<C>([&](int i) { return stage[i]; }, b.S, (uint32_t)b.r_lo, sh, dummy);
   }
 
   // One ordered pass: kept-for-sure (key > hi) and candidates (lo <= key <= hi).
-  // Chunks of 8192 scores are loaded coalesced one chunk ahead (kept raw until
+  // Chunks (2048 scores, 8192 in the wide shape) are loaded coalesced one chunk ahead (kept raw until
   // staged, so that no conversion waits on the loads early), staged in LDS
   // with a pad word per 8 keys, and read back as 8 consecutive keys per
   // thread (bank-conflict free); the block scan orders the threads' lists.
@@ -482,7 +539,7 @@ __device__ void select_staged(KeyAt key_at, RawAt raw_at, Conv conv, int n, int 
   float nxt[C::kPer];
   auto load_chunk = [&](int base) {
 #pragma unroll
-    for (int j = 0; j < C::kPer; ++j) nxt[j] = raw_at(min(base + j * C::kThreads + tid, n - 1));
+    for (int j = 0; j < C::kPer; ++j) nxt[j] = rs.raw(min(base + j * C::kThreads + tid, n - 1));
   };
   load_chunk(0);
   uint32_t gcnt = 0, ccnt = 0;
@@ -490,7 +547,7 @@ __device__ void select_staged(KeyAt key_at, RawAt raw_at, Conv conv, int n, int 
 #pragma unroll
     for (int j = 0; j < C::kPer; ++j) {
       const int p = base + j * C::kThreads + tid;
-      stage[pad(j * C::kThreads + tid)] = p < n ? conv(nxt[j]) : 0u;
+      stage[pad(j * C::kThreads + tid)] = p < n ? rs.conv(nxt[j]) : 0u;
     }
     if (base + C::kChunk < n) load_chunk(base + C::kChunk);  // uniform
     __syncthreads();
@@ -525,10 +582,7 @@ __device__ void select_staged(KeyAt key_at, RawAt raw_at, Conv conv, int n, int 
   }
   const bool ok = gcnt < (uint32_t)kk && gcnt + ccnt >= (uint32_t)kk &&
                   gcnt <= (uint32_t)C::kSure && ccnt <= (uint32_t)C::kCand;
-  if (!ok) {  // uniform: every thread holds the same counts
-    select_general<C>(key_at, n, kk, out, sh);
-    return;
-  }
+  if (!ok) return false;  // uniform: every thread holds the same counts
 
   // T among the candidates: rank kk - gcnt.
   const uint32_t r = (uint32_t)kk - gcnt;
@@ -560,28 +614,33 @@ __device__ void select_staged(KeyAt key_at, RawAt raw_at, Conv conv, int n, int 
   const int32_t* kept_c = reinterpret_cast<const int32_t*>(stage);
   for (int a = tid; a < (int)gcnt; a += C::kThreads) {
     const int32_t p = sh.gpos[a];
-    out[a + lower_bound_lds(kept_c, (int)r, p)] = p;
+    out.put(a + lower_bound_lds(kept_c, (int)r, p), p);
   }
-  for (int b = tid; b < (int)r; b += C::kThreads) {
-    const int32_t p = kept_c[b];
-    out[b + lower_bound_lds(sh.gpos, (int)gcnt, p)] = p;
+  for (int e = tid; e < (int)r; e += C::kThreads) {
+    const int32_t p = kept_c[e];
+    out.put(e + lower_bound_lds(sh.gpos, (int)gcnt, p), p);
   }
+  return true;
 }
 
-// TOP-kk of key_at(0 .. n-1) by (key desc, position asc), written to out[0 ..
-// kk) in ascending position order (0 < kk < n). raw_at / conv: a score as loaded,
-// and its key (loads kept apart from conversions).
-template <class C, class KeyAt, class RawAt, class Conv>
-__device__ __forceinline__ void select_unit(KeyAt key_at, RawAt raw_at, Conv conv, int n, int kk,
-                                            int32_t* out, SelShared<C>& sh) {
-  if (n <= C::kDirect / 2)
-    select_direct<C, C::kDirect / 2 / C::kThreads>(raw_at, conv, n, kk, out, sh);
-  else if (n <= C::kDirect)
-    select_direct<C, C::kDirect / C::kThreads>(raw_at, conv, n, kk, out, sh);
-  else if constexpr (C::kWide)
-    select_sampled<C>(key_at, raw_at, conv, n, kk, out, sh);
-  else
-    select_staged<C>(key_at, raw_at, conv, n, kk, out, sh);
+// TOP-kk of the ranked scores by (key desc, position asc), written to out at
+// 0 .. kk in ascending position order (0 < kk < n).
+template <class C, int DIR>
+__device__ __forceinline__ void select_unit(const RankedScores<DIR>& rs, int kk,
+                                            const SelOut<DIR>& out, SelShared<C>& sh) {
+  if (rs.n <= C::kDirect / 2) {
+    select_direct<C, C::kDirect / 2 / C::kThreads>(rs, kk, out, sh);
+  } else if (rs.n <= C::kDirect) {
+    select_direct<C, C::kDirect / C::kThreads>(rs, kk, out, sh);
+  } else {
+    bool done;
+    if (C::kWide && sel_wide_path(rs.n, kk) == SelPath::kSampled) {
+      if constexpr (C::kWide) done = select_sampled(rs, kk, out, sh);
+    } else {
+      done = select_staged(rs, kk, out, sh);
+    }
+    if (!done) select_general(rs, kk, out, sh);
+  }
 }
 
 // The complement is ranked instead of the kept tokens when it is the smaller
@@ -616,12 +675,26 @@ __global__ __launch_bounds__(C::kThreads) void select_kernel(Geo g, const float*
   // (~key desc, reversed position asc)), then emit every other position.
   const bool evicts = ranks_evicted<C>(n, kk);
   const int m = n - kk;
+  if (!evicts) {
+    for (int j = kk_all + tid; j < budget; j += C::kThreads) out[j] = -1;
+    for (int j = tid; j < npro; j += C::kThreads) out[kk + j] = n + j;
+    if (kk == 0) return;
+    if (kk == n) {
+      for (int j = tid; j < n; j += C::kThreads) out[j] = j;
+      return;
+    }
+  }
+  // evicted: as reversed positions, ascending (the candidates' keys are no
+  // longer read when they are written)
+  int32_t* rev = reinterpret_cast<int32_t*>(sh.ckey);
+  if constexpr (!C::kWide) {  // (compiled twice, the narrow shape's registers spill)
+    select_unit(RankedScores<kEither>{s, n, evicts}, evicts ? m : kk, SelOut<kEither>{out, rev, evicts}, sh);
+  } else if (evicts) {
+    select_unit(RankedScores<kReverse>{s, n, true}, m, SelOut<kReverse>{out, rev, true}, sh);
+  } else {
+    select_unit(RankedScores<kForward>{s, n, false}, kk, SelOut<kForward>{out, rev, false}, sh);
+  }
   if (evicts) {
-    // evicted, as reversed positions ascending (the candidates' keys are no
-    // longer read when they are written)
-    int32_t* rev = reinterpret_cast<int32_t*>(sh.ckey);
-    select_unit<C>([&](int i) { return ~score_key(s[n - 1 - i]); }, [&](int i) { return s[n - 1 - i]; },
-                [](float f) { return ~score_key(f); }, n, m, rev, sh);
     __syncthreads();
     auto evicted = [&](int j) { return n - 1 - rev[m - 1 - j]; };  // ascending
     if (slots) {
@@ -661,17 +734,7 @@ __global__ __launch_bounds__(C::kThreads) void select_kernel(Geo g, const float*
       const int c = lower_bound_lds(sh.kept, m, i);
       if (c == m || sh.kept[c] != i) out[i - c] = i;
     }
-    return;
   }
-  for (int j = kk_all + tid; j < budget; j += C::kThreads) out[j] = -1;
-  for (int j = tid; j < npro; j += C::kThreads) out[kk + j] = n + j;
-  if (kk == 0) return;
-  if (kk == n) {
-    for (int j = tid; j < n; j += C::kThreads) out[j] = j;
-    return;
-  }
-  select_unit<C>([&](int i) { return score_key(s[i]); }, [&](int i) { return s[i]; },
-              [](float f) { return score_key(f); }, n, kk, out, sh);
 }
 
 // The narrow shape: many units, each ranking at most half of its lists (the

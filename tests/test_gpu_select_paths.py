@@ -1,7 +1,8 @@
 """TOP-B selection and the evicted-slot lists at the lengths where the selection
 changes its path (every key in a register, sampled, staged; kept or evicted
 tokens ranked; the bitmap's end), in both launch shapes, on scores with many
-ties, NaN and -0: bit for bit the oracle's rule."""
+ties, NaN and -0: bit for bit the oracle's rule. The result is the same on every
+path: which one a unit takes is counted by test_select_bracket.py."""
 
 import numpy as np
 import pytest
@@ -41,6 +42,11 @@ NARROW = [2047, 2048, 2049, 4096, 4097, 9000]
     (1, 1, WIDE[:12], 8190, 0),
     (4, 64, NARROW, 257, 16),     # 1536 units: the narrow shape
     (4, 64, [2176, 2100, 2049, 1900, 2304, 2048], 2048, 5),
+    # large budgets and long contexts: bands of a larger sample, kept and evicted
+    (1, 1, [131072, 262145, 20000, 8192], 8192, 0),
+    (1, 1, [200001, 524288], 2048, 7),
+    (1, 1, [40000, 12000, 8192, 3000], 7900, 9),
+    (1, 2, [40000, 131072], 36000, 0),
 ])
 def test_paths(jacap, kind, layers, heads, lens, budget, protect):
     rng = np.random.default_rng(7)
