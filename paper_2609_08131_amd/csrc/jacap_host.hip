@@ -82,11 +82,12 @@ Workspace layout(const jacap_config* c, const jacap_batch* b, bool greedy = fals
   w.mfma = c->dtype == JACAP_DTYPE_BF16;
   w.kchunk = kKChunk;
   w.kchunks = (maxn + kKChunk - 1) / kKChunk;
-  // Weight chunks: kWChunk tokens, halved (down to kWChunkMin) while the batch's
-  // tokens fill fewer than kSmallBlocks workgroups (8 units of 8192 tokens: 7.9 us
-  // at 4096, 5.5 us at 1024).
+  // Weight chunks: kWChunk tokens, halved (down to kWChunkMin) while the grid has
+  // fewer than kSmallBlocks workgroups, those past short sequences' ends among them
+  // (8 units of 8192 tokens: 7.9 us at 4096, 5.5 us at 1024; 2400 units of 17 tokens and
+  // 8 of 4000: 14 us at 4096, 26 us at 1024).
   w.wchunk = kWChunk;
-  while (w.wchunk > kWChunkMin && LHT / w.wchunk < kSmallBlocks) w.wchunk /= 2;
+  while (w.wchunk > kWChunkMin && U * ((maxn + w.wchunk - 1) / w.wchunk) < kSmallBlocks) w.wchunk /= 2;
   w.wchunks = (maxn + w.wchunk - 1) / w.wchunk;
   w.gchunk = w.mfma ? kGChunkMfma : kGChunkPrecise;
   // Larger chunks write and re-read fewer partials. The longest sequence is
@@ -152,16 +153,25 @@ Workspace layout(const jacap_config* c, const jacap_batch* b, bool greedy = fals
   w.z = take(4 * LHT);
   w.kappa = take(4 * LHT);
   w.cstat = take(8 * U * (int64_t)w.kchunks);
-  // Batches whose K pass would not fill the chip take smaller chunks (8 units of
-  // 8192 bf16 tokens 12.0 us at 1024 and 8.1 us at 256; 512 fp32 tokens 13.7 and
-  // 6.5 us). Their statistics, which the weight pass consumes, are held where a
-  // later pass writes (`spare` bytes at `at`), if they fit.
-  auto small_chunks = [&](size_t at, int64_t spare) {
+  // The K pass (DIAG) of batches whose tokens would not fill the chip. Unequal
+  // sequences are spread over the XCDs, and smaller chunks taken (8 units of 8192
+  // bf16 tokens 12.0 us at 1024 and 8.1 us at 256; 512 fp32 tokens 13.7 and 6.5 us) --
+  // of bf16 keys, which cost little per token, while the grid has fewer than
+  // kSmallBlocks workgroups at 1024, those past short sequences' ends among them (128
+  // units of 16 to 4096 tokens 22.7 us at 1024, 25.6 at 256; fp32 45 and 41). Measured:
+  // 2400 units of 17 tokens and 8 of 4000, bf16, 219 us unspread, 48 here. The small
+  // chunks' statistics, which the weight pass consumes, are held where a later pass
+  // writes (`spare` bytes at `at`), if they fit.
+  w.kgrid = w.kchunks;
+  auto small_batch = [&](size_t at, int64_t spare) {
+    if (c->cov_mode != JACAP_COV_DIAG || LHT / kKChunk >= kSmallBlocks) return;
     const int64_t n = (maxn + kKChunkMin - 1) / kKChunkMin;
-    if (c->cov_mode != JACAP_COV_DIAG || LHT / kKChunk >= kSmallBlocks || 8 * U * n > spare) return;
-    w.kchunk = kKChunkMin;
-    w.kchunks = (int)n;
-    w.cstat = at;
+    if (8 * U * n <= spare && (w.mfma ? U * w.kchunks < kSmallBlocks : U * n <= kSmallGridMax)) {
+      w.kchunk = kKChunkMin;
+      w.kchunks = (int)n;
+      w.cstat = at;
+    }
+    w.kgrid = LHT != U * maxn ? spread_chunks(w.kchunks) : w.kchunks;
   };
   w.wgt = take(4 * LHT);
   if (greedy) {
@@ -171,14 +181,14 @@ Workspace layout(const jacap_config* c, const jacap_batch* b, bool greedy = fals
     w.gent = take(sizeof(GreedyEntry) * U * nblk);
     // the factor of Lambda_Q on the FULL covariance's triangular K pass
     w.lfrag = take(w.mfma && c->cov_mode == JACAP_COV_FULL ? 2 * U * nlp * 2 * 64 * 8 : 8);
-    small_chunks(w.gc, 8 * LHT);
+    small_batch(w.gc, 8 * LHT);
     w.total = o;
     return w;
   }
   w.hscore = take(V > 1 ? 4 * LHT : 4);
   w.kept = take(4 * (int64_t)b->num_seqs * c->num_layers * c->num_kv_heads * std::max(c->budget_k, 1));
   w.gram = take((size_t)std::max(mfma_part_bytes, fp64_part_bytes));
-  small_chunks(w.gram, std::max(mfma_part_bytes, fp64_part_bytes));
+  small_batch(w.gram, std::max(mfma_part_bytes, fp64_part_bytes));
   w.gram_red = take(8 * U * npair * 256);
   w.lfrag = take(w.mfma ? 2 * U * nlp * 2 * 64 * 8 : 8);
   w.total = o;

@@ -16,6 +16,7 @@ constexpr int kThreads = 256;        // 4 wave64 per workgroup
 constexpr int kKChunk = 1024;        // tokens per workgroup in the K pass
 constexpr int kKChunkMin = 256;      // ... of batches that would not fill the chip (DIAG)
 constexpr int kSmallBlocks = 2 * 256; // fewer workgroups than this leave compute units idle
+constexpr int kSmallGridMax = 1 << 20; // workgroups of a grid of small chunks: at most
 constexpr int kFullMaxQ = 256;       // window queries the FULL-covariance MFMA K pass stages
 // FULL covariance: units of at least this many tokens take kappa from the
 // triangular factor of Lambda_Q (a fixed per-unit cost that long units repay).
@@ -165,6 +166,11 @@ __device__ __forceinline__ RefineCut refine_cut(int R, int maxn, int slots) {
   return {(maxn + tok - 1) / tok, tok};
 }
 
+// Chunks per unit in a unit-major grid of unequal sequences: an odd number (the last
+// one may be empty). Workgroups go to the 8 XCDs in turn, so with a multiple of 8 the
+// first chunk of every unit, all that a short sequence has, would be on one of them.
+inline int spread_chunks(int nchunks) { return nchunks | 1; }
+
 inline int64_t chunked_grid(const Geo& g, int nchunks) {
   const int64_t pairs = (int64_t)nchunks * (g.U / g.V);
   return g.V == 1 ? pairs : (pairs + 7) / 8 * 8 * g.V;
@@ -199,6 +205,7 @@ struct Workspace {
   size_t gent;     // GreedyEntry [U][ceil(maxn / 256)]  greedy: best of each 256-position block
   size_t total;
   int kchunks, kchunk, wchunks, wchunk, gchunks, gchunk, gparts, lchunks, lchunk;
+  int kgrid;            // chunks per unit in the grid of the DIAG K pass (some may be empty)
   int pchunks, pchunk;  // chunks of the fp64 Gram pass over every unit (fp32 inputs)
   int pslots;           // fp64 partials the Gram buffer holds
   int plchunks, plchunk;  // chunks of the fp64 leverage pass over every unit

@@ -342,10 +342,10 @@ template <typename T, int D, bool FULL, int KC>
 __global__ __launch_bounds__(kThreads) void kpass_kernel(
     Geo g, const T* __restrict__ k, const double* __restrict__ mu, const double* __restrict__ lam,
     const float* __restrict__ lamfull, float* __restrict__ zout, float* __restrict__ kout,
-    float2* __restrict__ cstat, int kchunks, double inv_scale, uint32_t* status,
+    float2* __restrict__ cstat, int kchunks, int gridc, double inv_scale, uint32_t* status,
     uint32_t* uflags) {
   int u, chunk;
-  if (!grid_unit_chunk<false>(g, kchunks, u, chunk)) return;
+  if (!grid_unit_chunk<false>(g, gridc, u, chunk)) return;
   const Unit un = decode_unit(g, u);
   const int base = chunk * KC;
   if (base >= un.n) return;
@@ -453,10 +453,10 @@ template <int D, int KC>
 __global__ __launch_bounds__(kThreads) void kpass_quad_kernel(
     Geo g, const uint16_t* __restrict__ k, const double* __restrict__ mu,
     const double* __restrict__ lam, float* __restrict__ zout, float* __restrict__ kout,
-    float2* __restrict__ cstat, int kchunks, double inv_scale, uint32_t* status,
+    float2* __restrict__ cstat, int kchunks, int gridc, double inv_scale, uint32_t* status,
     uint32_t* uflags) {
   int u, chunk;
-  if (!grid_unit_chunk<false>(g, kchunks, u, chunk)) return;
+  if (!grid_unit_chunk<false>(g, gridc, u, chunk)) return;
   const Unit un = decode_unit(g, u);
   const int base = chunk * KC;
   if (base >= un.n) return;
@@ -949,20 +949,21 @@ __global__ __launch_bounds__(kThreads, 2) void kpass_tri_kernel(
 }
 
 template <typename T, int D>
-static void kpass_dispatch(const Launch& L, const void* k, bool full, dim3 grid, double inv_scale) {
+static void kpass_dispatch(const Launch& L, const void* k, bool full, double inv_scale) {
   const Geo& g = L.geo;
+  const dim3 grid((unsigned)chunked_grid(g, L.ws.kgrid));
   auto args = [&](auto kern) {
     kern<<<grid, kThreads, 0, L.stream>>>(
         g, (const T*)k, ws_ptr<double>(L.wsp, L.ws.mu), ws_ptr<double>(L.wsp, L.ws.lam),
         ws_ptr<float>(L.wsp, L.ws.lamfull), ws_ptr<float>(L.wsp, L.ws.z),
-        ws_ptr<float>(L.wsp, L.ws.kappa), ws_ptr<float2>(L.wsp, L.ws.cstat), L.ws.kchunks,
+        ws_ptr<float>(L.wsp, L.ws.kappa), ws_ptr<float2>(L.wsp, L.ws.cstat), L.ws.kchunks, L.ws.kgrid,
         inv_scale, ws_ptr<uint32_t>(L.wsp, L.ws.status), ws_ptr<uint32_t>(L.wsp, L.ws.uflags));
   };
   auto quad = [&](auto kern) {
     kern<<<grid, kThreads, 0, L.stream>>>(
         g, (const uint16_t*)k, ws_ptr<double>(L.wsp, L.ws.mu), ws_ptr<double>(L.wsp, L.ws.lam),
         ws_ptr<float>(L.wsp, L.ws.z), ws_ptr<float>(L.wsp, L.ws.kappa),
-        ws_ptr<float2>(L.wsp, L.ws.cstat), L.ws.kchunks, inv_scale,
+        ws_ptr<float2>(L.wsp, L.ws.cstat), L.ws.kchunks, L.ws.kgrid, inv_scale,
         ws_ptr<uint32_t>(L.wsp, L.ws.status), ws_ptr<uint32_t>(L.wsp, L.ws.uflags));
   };
   const bool small = L.ws.kchunk == kKChunkMin;
@@ -1019,11 +1020,11 @@ hipError_t launch_kpass(const Launch& L, const void* k, const void* q) {
     return hipGetLastError();
   }
   if (g.D == 128) {
-    if (bf) kpass_dispatch<uint16_t, 128>(L, k, full, grid, inv_scale);
-    else kpass_dispatch<float, 128>(L, k, full, grid, inv_scale);
+    if (bf) kpass_dispatch<uint16_t, 128>(L, k, full, inv_scale);
+    else kpass_dispatch<float, 128>(L, k, full, inv_scale);
   } else {
-    if (bf) kpass_dispatch<uint16_t, 64>(L, k, full, grid, inv_scale);
-    else kpass_dispatch<float, 64>(L, k, full, grid, inv_scale);
+    if (bf) kpass_dispatch<uint16_t, 64>(L, k, full, inv_scale);
+    else kpass_dispatch<float, 64>(L, k, full, inv_scale);
   }
   return hipGetLastError();
 }

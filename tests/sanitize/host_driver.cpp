@@ -9,6 +9,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "jacap.h"
@@ -276,6 +277,39 @@ static void run_gram_chunks() {
       }
 }
 
+// K-pass and weight chunks of small batches: no more workgroups for a longest length
+// that few or no sequences have, and unequal sequences' first chunks on every XCD.
+static void run_small_batches() {
+  struct { int heads, seqs, n, dtype; int64_t maxn; bool small; } t[] = {
+      {8, 1, 8192, JACAP_DTYPE_BF16, 8192, true},     // one layer
+      {8, 8, 1024, JACAP_DTYPE_BF16, 1024, true},
+      {8, 8, 1024, JACAP_DTYPE_BF16, 131072, false},  // a declared length far above the real ones
+      {8, 8, 1024, JACAP_DTYPE_FP32, 131072, true},
+      {8, 16, 100, JACAP_DTYPE_BF16, 32768, false},
+      {4095, 16, 1, JACAP_DTYPE_FP32, 1 << 17, false},  // 65520 units: the grid would be 2^25
+  };
+  for (const auto& x : t) {
+    Shape s = {1, x.heads, x.heads, 64, 4, 16, x.seqs, {}, x.dtype, JACAP_COV_DIAG, JACAP_GQA_POOLED,
+               JACAP_RIDGE_SCALAR, 0, 1.0f};
+    for (int i = 0; i < x.seqs; ++i) s.lens[i] = x.n;
+    jacap_config c;
+    jacap_batch b;
+    int32_t offs[17];
+    size_t ws = 0;
+    fill(s, &c, &b, offs);
+    b.max_seq_len = (int32_t)x.maxn;
+    EXPECT(jacap_workspace_size(&c, &b, &ws) == JACAP_OK);
+    EXPECT(jacap_score(&c, &b, fake(1), fake(2), fake(3), (float*)fake(4), fake(1000), ws, nullptr) == JACAP_OK);
+    const int64_t U = (int64_t)x.heads * x.seqs;
+    const auto& l = stub::last;
+    EXPECT((l.kchunk < 1024) == x.small);
+    EXPECT((int64_t)l.kchunks * l.kchunk >= x.maxn && l.kgrid >= l.kchunks);
+    EXPECT(x.n == x.maxn ? l.kgrid == l.kchunks : l.kgrid % 2 == 1);
+    EXPECT(U * l.kgrid <= (1 << 24));  // workgroups of 256 threads that a launch takes
+    EXPECT(U * l.wchunks <= std::max<int64_t>(2 * 512, U * ((x.maxn + 4095) / 4096)));
+  }
+}
+
 int main() {
   const Shape shapes[] = {
       // tiny fp32; one Llama layer; long128k; ragged lengths; per-head; FULL; W_O; token-free
@@ -298,6 +332,7 @@ int main() {
     run_valid(s, name);
   }
   run_gram_chunks();
+  run_small_batches();
   run_invalid();
   run_status();
   if (failures) {

@@ -12,6 +12,7 @@ struct Launch {
   int units, maxn;
   size_t ws_total;
   int gchunks, pchunks, pslots, plchunks;
+  int kchunk, kchunks, kgrid, wchunks;
 };
 extern int calls[kNumLaunchers];
 extern Launch last;
