@@ -102,6 +102,8 @@ static void run_valid(const Shape& s, const char* name) {
     const bool per_head = s.gqa == JACAP_GQA_PER_HEAD && s.Hq > s.H;
     EXPECT(stub::calls[stub::kHeadMean] == (per_head ? 1 : 0));
     EXPECT(stub::last.ws_total <= ws);
+    // where the GPU tests read which units took the fp64 path
+    EXPECT(stub::last.uflags == 256 && stub::unit_refine == 1u << 8);
     // every unit of fp32 inputs has fp64 Gram partials of its own, wherever it lies
     EXPECT(bf || (int64_t)stub::last.units * stub::last.pchunks <= stub::last.pslots);
   } else {

@@ -9,13 +9,14 @@
 namespace stub {
 int calls[kNumLaunchers];
 Launch last;
+extern const unsigned unit_refine = jacap::kUnitRefine;
 }  // namespace stub
 
 namespace jacap {
 
 static hipError_t note(int which, const Launch& L) {
   ++stub::calls[which];
-  stub::last = {L.geo.U, L.geo.maxn, L.ws.total, L.ws.gchunks, L.ws.pchunks, L.ws.pslots, L.ws.plchunks,
+  stub::last = {L.geo.U, L.geo.maxn, L.ws.total, L.ws.uflags, L.ws.gchunks, L.ws.pchunks, L.ws.pslots, L.ws.plchunks,
                 L.ws.kchunk, L.ws.kchunks, L.ws.kgrid, L.ws.wchunks};
   return hipSuccess;
 }

@@ -1,8 +1,9 @@
 """The fp64 path (Gram and leverage products on the fp64 MFMA) at the sizes where
 its tiles end: every unit of fp32 inputs, the marked units of bf16 inputs, from
 few marked units of a batch to all of them. Tolerance: the stated one of the
-scores (fp32 1e-5; bf16 units on this path are held to the fp32 one too, since
-their products and sums are fp64 and only the fp32 weights round)."""
+scores (fp32 1e-5, bf16 1e-3); bf16 units on this path are held to 5e-5, since
+their products and sums are fp64 and only the weights round (their K pass sums
+in fp32)."""
 
 import numpy as np
 import pytest
@@ -10,15 +11,18 @@ import torch
 
 from jacap_synth import make_case
 
-from helpers import FP32_TOL, gpu_unit_scores, oracle_unit, run_gpu, score_errors, unit_list
+from helpers import BF16_TOL, FP32_TOL, gpu_unit_scores, oracle_unit, run_gpu, score_errors, unit_list
 
 pytestmark = pytest.mark.gpu
 
-MARKED = 1 << 8   # the workspace's per-unit flag of the fp64 path
+# The workspace's per-unit flags and the one of the fp64 path (both are pinned by
+# the host driver, tests/sanitize/host_driver.cpp).
+FLAGS_AT, MARKED = 256, 1 << 8
+MARKED_TOL = 5e-5
 
 
 def _marked_units(prob, units):
-    flags = prob.ws[256:256 + 4 * units].view(torch.int32).cpu().numpy()
+    flags = prob.ws[FLAGS_AT:FLAGS_AT + 4 * units].view(torch.int32).cpu().numpy()
     return (flags & MARKED) != 0
 
 
@@ -45,10 +49,9 @@ def test_every_unit_at_tile_edges(dtype, d, token_major):
     for i, (b, l, h) in enumerate(units):
         o = oracle_unit(case, b, l, h, 64, ridge=0.0 if dtype == "bf16" else 1.0)
         err = score_errors(gpu_unit_scores(case, prob, b, l, h), o["scores"])
-        assert err.max() <= (FP32_TOL if dtype == "fp32" else 1e-3), (b, l, h, float(err.max()))
+        assert err.max() <= (FP32_TOL if dtype == "fp32" else BF16_TOL), (b, l, h, float(err.max()))
         if dtype == "bf16" and marked[i]:
-            # the score's own error: its weight's (fp32 K pass sums, a few 1e-6)
-            assert err.max() <= 5e-5, (b, l, h, float(err.max()))
+            assert err.max() <= MARKED_TOL, (b, l, h, float(err.max()))
 
 
 @pytest.mark.parametrize("d", [128, 64])
@@ -68,9 +71,11 @@ def test_few_marked_units_of_a_large_batch(d):
     marked = _marked_units(prob, len(units))
     assert 3 <= marked.sum() <= len(units) // 2
     assert all(marked[units.index(x)] for x in [(39, 1, 2), (39, 1, 3), (1, 0, 0)])
-    for b, l, h in [(39, 1, 2), (39, 1, 3), (1, 0, 0), (39, 0, 0), (5, 1, 1)]:
+    for i, (b, l, h) in enumerate(units):
+        if not marked[i] and (b, l, h) not in [(39, 0, 0), (5, 1, 1)]:
+            continue
         o = oracle_unit(case, b, l, h, 32, ridge=1.0)
         err = score_errors(gpu_unit_scores(case, prob, b, l, h), o["scores"])
-        assert err.max() <= 1e-3, (b, l, h, float(err.max()))
+        assert err.max() <= (MARKED_TOL if marked[i] else BF16_TOL), (b, l, h, float(err.max()))
     again, _ = run_gpu(case, 32, ridge=1.0)   # the list's order does not show
     assert torch.equal(again.scores, prob.scores)
