@@ -107,7 +107,6 @@ Workspace layout(const jacap_config* c, const jacap_batch* b, bool greedy = fals
     w.gchunk = (int)std::min<int64_t>(std::max<int64_t>(per, kGChunkMfma), kGChunkMfmaMax);
   }
   w.gchunks = (maxn + w.gchunk - 1) / w.gchunk;
-  w.gparts = 1;
   // Leverage chunks: kLChunkMfma tokens, halved (down to kLChunkMfmaMin) while
   // the grid would have fewer than kLevMinBlocks blocks.
   w.lchunk = w.mfma ? kLChunkMfma : kLChunkPrecise;

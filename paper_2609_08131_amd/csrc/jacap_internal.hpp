@@ -204,7 +204,7 @@ struct Workspace {
   size_t gst;      // int32  [L][H][T]       greedy: picks made at that time (-1 = taken)
   size_t gent;     // GreedyEntry [U][ceil(maxn / 256)]  greedy: best of each 256-position block
   size_t total;
-  int kchunks, kchunk, wchunks, wchunk, gchunks, gchunk, gparts, lchunks, lchunk;
+  int kchunks, kchunk, wchunks, wchunk, gchunks, gchunk, lchunks, lchunk;
   int kgrid;            // chunks per unit in the grid of the DIAG K pass (some may be empty)
   int pchunks, pchunk;  // chunks of the fp64 Gram pass over every unit (fp32 inputs)
   int pslots;           // fp64 partials the Gram buffer holds
@@ -225,13 +225,6 @@ struct GreedyEntry {
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) {
   return __uint_as_float(((uint32_t)b) << 16);
-}
-
-// float -> bfloat16, round to nearest even (inputs here are finite).
-__device__ __forceinline__ uint16_t f32_to_bf16(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
 }
 
 template <typename T>
@@ -276,11 +269,6 @@ __device__ __forceinline__ float wave_sum(float v) {
 __device__ __forceinline__ int wave_min(int v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o));
-  return v;
-}
-__device__ __forceinline__ double wave_max_f64(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
   return v;
 }
 __device__ __forceinline__ double wave_sum(double v) {

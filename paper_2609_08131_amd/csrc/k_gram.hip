@@ -282,7 +282,7 @@ __device__ __forceinline__ void gram_wave(const GramArgs& ga, uint16_t* tiles, f
 template <int D, int NT, int POL>
 __global__ __launch_bounds__(kThreads, 2) void gram_mfma_kernel(
     Geo g, const uint16_t* __restrict__ v, const float* __restrict__ wbuf,
-    const uint32_t* __restrict__ uflags, float* __restrict__ partials, int gchunks, int gchunk) {
+    float* __restrict__ partials, int gchunks, int gchunk) {
   constexpr int NB = D / 16;
   constexpr int NPAIR = NB * (NB + 1) / 2;
   constexpr int TILE = kGramStep * kGramPitch;
@@ -338,7 +338,8 @@ __global__ __launch_bounds__(kThreads, 2) void gram_mfma_kernel(
 // marked units of 2176 tokens among 4096: 986 us and 25 us. Held to 128 VGPRs
 // (fp32 rows one step per turn) two workgroups share a compute unit and one's
 // loads run under the other's products: 8 fp32 sequences of 0 to 8193 tokens,
-// 8 heads, 72 us with one, 62 us with two.
+// 8 heads, 72 us with one, 62 us with two -- at d = 128 for 7 (bf16) and 2 (fp32)
+// spilled registers.
 //
 // Partial: block pair p (row-major over I <= J), entry i of lane l at
 // p * 256 + 64 i + l = M[NB (4 i + l / 16) + I][NB (l % 16) + J].
@@ -484,13 +485,12 @@ __global__ __launch_bounds__(kF64Threads, 4) void gram_f64_kernel(
 hipError_t launch_gram(const Launch& L, const void* v, bool refine) {
   const Geo& g = L.geo;
   const float* wb = ws_ptr<float>(L.wsp, L.ws.wgt);
-  const uint32_t* uf = ws_ptr<uint32_t>(L.wsp, L.ws.uflags);
   if (L.ws.mfma && !refine) {
     const dim3 grid((unsigned)chunked_grid(g, L.ws.gchunks));
     float* part = ws_ptr<float>(L.wsp, L.ws.gram);
     const uint16_t* vv = (const uint16_t*)v;
     auto go = [&](auto kern) {
-      kern<<<grid, kThreads, 0, L.stream>>>(g, vv, wb, uf, part, L.ws.gchunks, L.ws.gchunk);
+      kern<<<grid, kThreads, 0, L.stream>>>(g, vv, wb, part, L.ws.gchunks, L.ws.gchunk);
     };
     if (g.D == 128) {
       if (g.V > 1) go(gram_mfma_kernel<128, 2, kPolicyShared>);

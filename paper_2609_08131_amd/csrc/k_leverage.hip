@@ -187,6 +187,7 @@ __global__ __launch_bounds__(kThreads, 2) void leverage_f64_kernel(
   constexpr int TRIP = TT * 16 * (kThreads / 64);  // tokens per workgroup trip
   constexpr int WORDS = 4 * sizeof(T) / 4;     // 32-bit words of four channels
   // fp32 tiles are read after the previous trip: a second set of them would spill
+  // (the bf16 one does at d = 128, 10 registers)
   constexpr bool AHEAD = sizeof(T) == 2;
   static_assert(TRIP == kLChunkPreciseMin, "the smallest chunk is one trip");
   __shared__ __attribute__((aligned(16))) double X[NPAIR * 256];

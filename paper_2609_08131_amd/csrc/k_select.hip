@@ -412,10 +412,7 @@ __device__ __forceinline__ void select_direct(const RankedScores<DIR>& rs, int k
 #pragma unroll
   for (int j = 0; j < PER; ++j) raw[j] = rs.raw(min(pos(j), n - 1));
 #pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    k[j] = pos(j) < n ? rs.conv(raw[j]) : 0u;
-    if (PER > 4 && j % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // the keys' masks would spill
-  }
+  for (int j = 0; j < PER; ++j) k[j] = pos(j) < n ? rs.conv(raw[j]) : 0u;
   uint32_t above;
   const uint32_t T = rank_search<C, PER>(k, (uint32_t)kk, 0u, sh, par, above);
   emit_kept<C, PER>(k, T, (uint32_t)kk - above, sh, par,
@@ -687,7 +684,7 @@ __global__ __launch_bounds__(C::kThreads) void select_kernel(Geo g, const float*
   // evicted: as reversed positions, ascending (the candidates' keys are no
   // longer read when they are written)
   int32_t* rev = reinterpret_cast<int32_t*>(sh.ckey);
-  if constexpr (!C::kWide) {  // (compiled twice, the narrow shape's registers spill)
+  if constexpr (!C::kWide) {  // (16 keys per thread: 30 spilled scalar registers, 57 if compiled twice)
     select_unit(RankedScores<kEither>{s, n, evicts}, evicts ? m : kk, SelOut<kEither>{out, rev, evicts}, sh);
   } else if (evicts) {
     select_unit(RankedScores<kReverse>{s, n, true}, m, SelOut<kReverse>{out, rev, true}, sh);
