@@ -39,7 +39,8 @@ constexpr int kWChunk = 4096;        // tokens per workgroup in the weight pass:
 constexpr int kWChunkMin = 1024;     // ... and at least (batches that would not fill the chip)
 // The K pass sums a chunk's exp(z - max) terms (all but the max's own) as
 // exp(z - max + kRestShift) in fp32, so that they stay normal down to
-// z - max ~ -150 (a sharply peaked softmax at small temperature).
+// z - max ~ -150 (a sharply peaked softmax at small temperature); below that the
+// sum's logarithm is kept instead.
 constexpr float kRestShift = 64.0f;
 constexpr int kGreedyMaxLen = 524288; // longest sequence the greedy selection takes
 constexpr int kGreedyMaxD = 128;
@@ -189,7 +190,7 @@ struct Workspace {
   size_t wscale;   // double [U]             power of two by which the stored weights are scaled
   size_t z;        // float  [L][H][T]       centre logits
   size_t kappa;    // float  [L][H][T]       query response
-  size_t cstat;    // float2 [U][kchunks]    per-chunk (max, sum exp)
+  size_t cstat;    // float2 [U][kchunks]    per-chunk (max, sum exp or its logarithm)
   size_t wgt;      // float  [L][H][T]       importance weights (Eq. 8)
   size_t hscore;   // float  [L][H][G][T]    per-query-head scores (per-head GQA mode)
   size_t kept;     // int32  [B][L][H][budget] kept positions, staged by jacap_select_evicted

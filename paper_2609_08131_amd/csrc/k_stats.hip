@@ -279,7 +279,9 @@ __device__ __forceinline__ F group_sum(F v) {
 // the max (whose term is exactly 1). Kept apart from that 1, the rest keeps its
 // own relative precision when one token dominates the softmax, which
 // 1 - alpha of that token needs (it is the rest of Z over Z); the shift keeps
-// its terms out of fp32's subnormal range.
+// its terms out of fp32's subnormal range, and a rest that falls into it all the
+// same (every other token more than about 145 below the maximum) is stored as its
+// logarithm, a negative number.
 template <int KC>
 __device__ __forceinline__ void kpass_epilogue(const Unit& un, int u, int base, int64_t trow,
                                                const float* zsh, const float* ksq, float* red,
@@ -322,7 +324,20 @@ __device__ __forceinline__ void kpass_epilogue(const Unit& un, int u, int base, 
   for (int q = 0; q < ZPT; ++q)
     ex += (zv[q] == -INFINITY || q * kThreads + tid == first) ? 0.0f
                                                                : expf(zv[q] - m + kRestShift);
-  const float s = block_combine(wave_sum(ex), red, [](float a, float b) { return a + b; });
+  float s = block_combine(wave_sum(ex), red, [](float a, float b) { return a + b; });
+  if (s < 0x1p-116f) {  // the same in every thread
+    float m2 = -INFINITY;
+#pragma unroll
+    for (int q = 0; q < ZPT; ++q)
+      if (q * kThreads + tid != first) m2 = fmaxf(m2, zv[q]);
+    m2 = block_combine(wave_max(m2), red, [](float a, float b) { return fmaxf(a, b); });
+    float ex2 = 0.0f;
+#pragma unroll
+    for (int q = 0; q < ZPT; ++q)
+      ex2 += (zv[q] == -INFINITY || q * kThreads + tid == first) ? 0.0f : expf(zv[q] - m2);
+    const float s2 = block_combine(wave_sum(ex2), red, [](float a, float b) { return a + b; });
+    s = m2 > -INFINITY ? (m2 - m) + logf(s2) : 0.0f;
+  }
   if (tid == 0) cstat[(int64_t)u * kchunks + chunk] = make_float2(m, s);
 }
 
@@ -1038,8 +1053,8 @@ hipError_t launch_kpass(const Launch& L, const void* k, const void* q) {
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kThreads) void softmax_weights_kernel(
     Geo g, const float2* __restrict__ cstat, int kchunks, int kchunk, const float* __restrict__ zbuf,
-    const float* __restrict__ kbuf, double inv_d, int wchunks, int wchunk, double* __restrict__ scale_out,
-    float* __restrict__ wout) {
+    const float* __restrict__ kbuf, double inv_d, int wchunks, int wchunk, int max_half,
+    double* __restrict__ scale_out, float* __restrict__ wout) {
   int u, chunk;
   if (!grid_unit_chunk<false>(g, wchunks, u, chunk)) return;
   const int tid = threadIdx.x;
@@ -1067,7 +1082,8 @@ __global__ __launch_bounds__(kThreads) void softmax_weights_kernel(
   double rest = 0.0;
   for (int c = tid; c < nch; c += kThreads) {
     const double dm = (double)cs[c].x - (double)m;
-    rest += (c == cmax ? 0.0 : exp(dm)) + (double)cs[c].y * exp(dm - (double)kRestShift);
+    const double y = (double)cs[c].y;
+    rest += (c == cmax ? 0.0 : exp(dm)) + (y < 0.0 ? exp(dm + y) : y * exp(dm - (double)kRestShift));
   }
   rest = block_combine(wave_sum(rest), redd, [](double a, double b) { return a + b; });
   const double s = 1.0 + rest;  // Z
@@ -1075,11 +1091,14 @@ __global__ __launch_bounds__(kThreads) void softmax_weights_kernel(
   // that bound is tiny (a saturated softmax) the weights are stored times a
   // power of two that lifts its square to [1, 4), so that they stay inside
   // fp32's range; the ridge (or R) is scaled by the same power of two in the
-  // factorisation, which leaves every score w_i v_i^T A^{-1} v_i unchanged.
+  // factorisation, which leaves every score w_i v_i^T A^{-1} v_i unchanged. The rest
+  // of Z reaches down to 1e-308: the power is bounded (half of its exponent by
+  // max_half), so that it and the scaled ridge stay finite, and rho takes its square
+  // root before it is squared.
   const double rho_max = fmin(0.25, rest / s);
-  const double wscale = rho_max > 0.0 && rho_max < 0x1p-20 ? ldexp(1.0, -2 * ilogb(rho_max)) : 1.0;
-  if (chunk == 0 && tid == 0) scale_out[u] = wscale;
-  const double wfac = wscale * inv_d;
+  const int half = rho_max > 0.0 && rho_max < 0x1p-20 ? min(-ilogb(rho_max), max_half) : 0;
+  if (chunk == 0 && tid == 0) scale_out[u] = ldexp(1.0, 2 * half);
+  const double lift = ldexp(1.0, half);
   const int64_t trow = token_row(g, un);
   const int end = min(un.n, base + wchunk);
   // Eq. 8 per token: e = exp(z - m) from the fp32 exponential of the rounded
@@ -1092,8 +1111,8 @@ __global__ __launch_bounds__(kThreads) void softmax_weights_kernel(
     const float df = (float)dz;
     // far below the maximum the fp32 exponential would be subnormal
     const double e = df > -80.0f ? (double)expf(df) * (1.0 + (dz - (double)df)) : exp(dz);
-    const double rho = (e * invZ) * (((1.0 - e) + rest) * invZ);
-    return (float)(rho * rho * (double)kap * wfac);
+    const double rho = (e * invZ) * (((1.0 - e) + rest) * invZ) * lift;
+    return (float)(rho * rho * (double)kap * inv_d);
   };
   constexpr int U4 = 4;
   static_assert(kWChunkMin % (U4 * kThreads) == 0, "whole unrolled trips per chunk");
@@ -1114,10 +1133,14 @@ __global__ __launch_bounds__(kThreads) void softmax_weights_kernel(
 hipError_t launch_softmax_weights(const Launch& L) {
   const int wchunks = L.ws.wchunks > 0 ? L.ws.wchunks : 1;
   const dim3 grid((unsigned)chunked_grid(L.geo, wchunks));
+  // With a ridge (fp32, below 2^128; or R), a scale of 2^896 leaves its scores below
+  // fp32's range already; without one they do not depend on the scale.
+  const bool ridge = L.cfg->ridge_mode == JACAP_RIDGE_MATRIX || L.cfg->ridge > 0.0f;
+  const int max_half = ridge ? 448 : 511;
   softmax_weights_kernel<<<grid, kThreads, 0, L.stream>>>(
       L.geo, ws_ptr<float2>(L.wsp, L.ws.cstat), L.ws.kchunks, L.ws.kchunk,
       ws_ptr<float>(L.wsp, L.ws.z), ws_ptr<float>(L.wsp, L.ws.kappa), 1.0 / (double)L.geo.D, wchunks,
-      L.ws.wchunk,
+      L.ws.wchunk, max_half,
       ws_ptr<double>(L.wsp, L.ws.wscale), ws_ptr<float>(L.wsp, L.ws.wgt));
   return hipGetLastError();
 }
