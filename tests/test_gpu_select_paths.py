@@ -78,3 +78,20 @@ def test_paths(jacap, kind, layers, heads, lens, budget, protect):
                 assert np.array_equal(ev[b, l, h][:len(gone)], gone), (b, n, l, h)
                 assert np.all(ev[b, l, h][len(gone):] == -1)
         lo += n
+
+
+@pytest.mark.parametrize("n,budget", [(500, 60), (3000, 700), (20000, 300)])
+def test_subnormal_and_infinite_scores(jacap, n, budget):
+    """Order kept below fp32's normal range, and between it, -0, the infinities and NaN."""
+    rng = np.random.default_rng(n)
+    s = (rng.standard_normal(n) * 1e-41).astype(np.float32)
+    s[rng.random(n) < 0.05] = -0.0
+    s[rng.random(n) < 0.01] = np.inf
+    s[rng.random(n) < 0.01] = -np.inf
+    s[rng.random(n) < 0.01] = np.nan
+    z = torch.zeros((1, 1, n, 64), dtype=torch.bfloat16, device="cuda")
+    offs = torch.tensor([0, n], dtype=torch.int32, device="cuda")
+    prob = jacap.prepare(z[:, :, :1].unsqueeze(0), z, z, offs, [n], jacap.Params(budget_k=budget))
+    jacap.select(prob.cfg, prob.batch, torch.from_numpy(s).cuda().reshape(1, 1, n), prob.idx, prob.ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(prob.idx.cpu().numpy()[0, 0, 0], np.asarray(jo.select_top(s, budget)))
