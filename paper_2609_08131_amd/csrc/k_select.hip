@@ -17,9 +17,8 @@
 //   their ranking and emission -- as long as the candidates a sample leaves are few;
 // * staged: a larger sample brackets lo <= T <= hi, so that large budgets too leave
 //   few candidates: the pass collects the tokens with key > hi (kept for sure) and
-//   those of the band. At 8192 sample keys a band of 2 (4 sqrt(ks) + 16) of them (ks =
-//   budget x 8192 / n) outgrows the 8192-entry lists from about 12000 kept of 131072
-//   on.
+//   those of the band, in a list of 8192 each (the first is full from about 10000
+//   kept of 131072 on).
 // The pass checks that the bounds hold (fewer than budget tokens above hi, at
 // least budget at or above lo) and that the lists fit; otherwise the unit takes
 // the general path: a three-pass radix select over the scores (11 + 11 + 10
